@@ -1,10 +1,10 @@
-// Generated by gen_instances.py: F8 inputs, 256x256 tiles, A m-contiguous,
+// Generated by gen_instances.py: F8 inputs, 256x256 tiles (8 waves), A m-contiguous,
 // B n-contiguous; single and grouped launches, Stream-K and data-parallel entries.
 #include "sk_dispatch.hpp"
 
 namespace sk {
 KernelEntry pick_f8_256_nn(const KernelKey &k) {
-    return k.grouped ? entry<Dt::F8, 256, 256, false, false, true>(k.dp_only)
-                     : entry<Dt::F8, 256, 256, false, false, false>(k.dp_only);
+    return k.grouped ? entry<Dt::F8, 256, 256, false, false, true, 8>(k.dp_only)
+                     : entry<Dt::F8, 256, 256, false, false, false, 8>(k.dp_only);
 }
 }  // namespace sk

@@ -69,20 +69,19 @@ template <> struct DtTraits<Dt::F64> {
     static constexpr int MT = 16;   // MFMA output block edge
     using Acc = double;
     using Frag = f64x4;             // one 16x16 output block per lane
-    static constexpr int FRAG_N = 4;
 };
 template <> struct DtTraits<Dt::F16> {
-    static constexpr int E = 2, MT = 32, FRAG_N = 16;
+    static constexpr int E = 2, MT = 32;
     using Acc = float;
     using Frag = f32x16;
 };
 template <> struct DtTraits<Dt::BF16> {
-    static constexpr int E = 2, MT = 32, FRAG_N = 16;
+    static constexpr int E = 2, MT = 32;
     using Acc = float;
     using Frag = f32x16;
 };
 template <> struct DtTraits<Dt::F8> {
-    static constexpr int E = 1, MT = 32, FRAG_N = 16;
+    static constexpr int E = 1, MT = 32;
     using Acc = float;
     using Frag = f32x16;
 };
@@ -109,9 +108,11 @@ struct Cfg {
     static constexpr int BKS = KROW / E;        // k per staged k-tile
     static constexpr int SUB = BK / BKS;        // staged k-tiles per MAC-loop iteration
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;   // the wave's block of C
-    static constexpr int MT = DtTraits<D>::MT;
+    // MFMA block edge: the eight-wave tiles take the 16x16 forms (less power,
+    // see mac_loop_pp)
+    static constexpr int MT = NW == 8 ? 16 : DtTraits<D>::MT;
     static constexpr int FM = WTM / MT, FN = WTN / MT;
-    static constexpr int FRAG_N = DtTraits<D>::FRAG_N;
+    static constexpr int FRAG_N = MT * MT / 64;       // accumulators per lane of one block
     static constexpr int A_BYTES = BM * KROW, B_BYTES = BN * KROW;
     static constexpr int STAGE = A_BYTES + B_BYTES;
     // LDS k-tile buffers.  FP64 keeps three (its k-tiles carry half the
@@ -121,21 +122,33 @@ struct Cfg {
     static constexpr int NSTAGE = D == Dt::F64 ? 3 : (KROW == 64 ? 4 : 2);
     static constexpr int LDS = NSTAGE * STAGE;
     static constexpr int DMA_PER_KTILE = STAGE / DMA_ROUND;   // LDS-DMA loads per wave per staged k-tile
+    // the eight-wave 256x256 tiles: half-tile buffers and the two-group MAC
+    // loop (mac_loop_pp)
+    static constexpr bool PP = NW == 8;
+    // LDS objects holding the k-tile buffers: NSTAGE whole stages, or (PP)
+    // the halves A0 A1 B0 B1 of two stages
+    static constexpr int LDS_OBJ = PP ? STAGE / 4 : STAGE;
+    static_assert(!PP || (NSTAGE == 2 && BM == 256 && BN == 256 && E <= 2), "two stages of four 16 KiB halves");
+    // first row (column) within the tile of a wave's fragment row i (column
+    // j).  PP: a wave's block is split over the halves of the tile, so that
+    // a quarter of its MFMAs needs one half of A and one half of B.
+    __device__ static constexpr int frow(int wm, int i) {
+        return PP ? (i / (FM / 2)) * (BM / 2) + wm * (WTM / 2) + (i % (FM / 2)) * MT : wm * WTM + i * MT;
+    }
+    __device__ static constexpr int fcol(int wn, int j) {
+        return PP ? (j / (FN / 2)) * (BN / 2) + wn * (WTN / 2) + (j % (FN / 2)) * MT : wn * WTN + j * MT;
+    }
     // k-tile instruction order pinned for the scheduler (MFMAs interleaved
     // with the loads and fragment reads, barrier before the last k-step):
-    // measured faster for the 16-bit 256x256 tile (one workgroup, so one
-    // wave, per SIMD) and for FP8; slower for the 16-bit 128x128 tile (two
-    // workgroups per CU cover each other's stalls) and FP64, which keep the
-    // compiler's order
-    static constexpr bool ORDERED = NW == 4 && (D == Dt::F8 || (E == 2 && BM >= 256));
-    // the first fixup peer is staged through LDS (not for the 256x256 FP8
-    // tile, whose transpose-read fragments leave no registers for it)
-    static constexpr bool FIX_LDS = !(D == Dt::F8 && BM >= 256);
+    // measured faster for the FP8 128x128 tile; slower for the 16-bit
+    // 128x128 tile (two workgroups per CU cover each other's stalls) and
+    // FP64, which keep the compiler's order
+    static constexpr bool ORDERED = D == Dt::F8 && !PP;
     // peers whose partial fragments are loaded together in the fixup (the
     // 256x256 tiles have no registers for more than one at a time)
     static constexpr int PEER_BATCH = BM >= 256 ? 1 : 4;
     using Acc = typename DtTraits<D>::Acc;
-    using Frag = typename DtTraits<D>::Frag;
+    using Frag = std::conditional_t<MT == 16 && D != Dt::F64, f32x4, typename DtTraits<D>::Frag>;
     static constexpr int ACC_N = FM * FN * FRAG_N;     // accumulators per thread
     static constexpr int ACC_CHUNKS = ACC_N * (int)sizeof(Acc) / 16;
     static constexpr int SLOT_BYTES = BM * BN * (int)sizeof(Acc);
@@ -290,16 +303,36 @@ __device__ __forceinline__ void wait_dma_but() {
     asm volatile("" ::: "memory");
 }
 
-// The MAC loop's LDS k-tile buffers: separate LDS objects (NSTAGE of them
-// in use), selected by compile-time index.
+// The MAC loop's LDS buffers: separate LDS objects (NSTAGE k-tiles, or the
+// eight half-tiles of PP), selected by compile-time index in the MAC loop.
 struct LdsBufs {
-    char *b0, *b1, *b2, *b3;
+    char *b0, *b1, *b2, *b3, *b4, *b5, *b6, *b7;
     template <int I>
     __device__ __forceinline__ char *get() const {
         if constexpr (I == 0) return b0;
         else if constexpr (I == 1) return b1;
         else if constexpr (I == 2) return b2;
-        else return b3;
+        else if constexpr (I == 3) return b3;
+        else if constexpr (I == 4) return b4;
+        else if constexpr (I == 5) return b5;
+        else if constexpr (I == 6) return b6;
+        else return b7;
+    }
+    // object i of N at run time (selected as LDS offsets: values, not the
+    // members' addresses)
+    template <int N>
+    __device__ __forceinline__ char *at(int i) const {
+        using L = __attribute__((address_space(3))) char *;
+        auto o = [](char *p) { return (uint32_t)(uintptr_t)(L)p; };
+        const uint32_t o0 = o(b0), o1 = o(b1), o2 = o(b2);
+        uint32_t r = i == 0 ? o0 : i == 1 ? o1 : o2;
+        if constexpr (N > 3) {
+            const uint32_t o3 = o(b3), o4 = o(b4), o5 = o(b5), o6 = o(b6), o7 = o(b7);
+            const uint32_t lo = i & 2 ? (i & 1 ? o3 : o2) : (i & 1 ? o1 : o0);
+            const uint32_t hi = i & 2 ? (i & 1 ? o7 : o6) : (i & 1 ? o5 : o4);
+            r = i & 4 ? hi : lo;
+        }
+        return (char *)(L)(uintptr_t)r;
     }
 };
 
@@ -319,7 +352,8 @@ template <class C>
 struct Frag {
     static constexpr int CPM = (C::DT == Dt::F8) ? 2 : 1;          // chunks per lane per operand
     static constexpr int CHUNKS = C::KROW / 16;                     // chunks per staged LDS row
-    static constexpr int NSUB = (C::DT == Dt::F64) ? CHUNKS / 4 : CHUNKS / (2 * CPM);   // k-steps per staged k-tile
+    static constexpr int LG = 64 / C::MT;                           // lane groups along k
+    static constexpr int NSUB = CHUNKS / (LG * CPM);                // k-steps per staged k-tile
     // MFMAs and LDS fragment reads per k-step
     static constexpr int MFMAS = C::FM * C::FN * (C::DT == Dt::F64 ? 2 : 1);
     static constexpr int READS_PER_FRAG = C::DT == Dt::F8 ? 4 : 2;   // transpose / 8-byte reads
@@ -330,8 +364,7 @@ struct Frag {
 
 template <class C>
 __device__ __forceinline__ int frag_chunk(int ks, int q, int s) {
-    if constexpr (C::DT == Dt::F64) return ks * 4 + q;
-    else return ks * 2 * Frag<C>::CPM + q * Frag<C>::CPM + s;
+    return (ks * Frag<C>::LG + q) * Frag<C>::CPM + s;
 }
 
 // One 16-bit MFMA operand fragment from a !KC operand stage (k-rows of ROWS
@@ -446,6 +479,28 @@ __device__ __forceinline__ void read_frags(Frag<C> &f, const char *ldsA, const c
 
 __device__ __forceinline__ double lo_d(const u32x4 &x) { return u2d((uint64_t)x[0] | ((uint64_t)x[1] << 32)); }
 __device__ __forceinline__ double hi_d(const u32x4 &x) { return u2d((uint64_t)x[2] | ((uint64_t)x[3] << 32)); }
+
+// One fragment pair of one 16x16 block, accumulated (16-bit and FP8 types):
+// D = B_frag * A_frag, the transposed block (see the output layout)
+template <class C>
+__device__ __forceinline__ void mfma16(typename C::Frag &acc, const u32x4 (&a)[Frag<C>::CPM],
+                                       const u32x4 (&b)[Frag<C>::CPM]) {
+    if constexpr (C::DT == Dt::BF16) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b[0]),
+                                                      __builtin_bit_cast(bf16x8, a[0]), acc, 0, 0, 0);
+    } else if constexpr (C::DT == Dt::F16) {
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, b[0]),
+                                                     __builtin_bit_cast(f16x8, a[0]), acc, 0, 0, 0);
+    } else {
+        const i32x8 av = __builtin_shufflevector(__builtin_bit_cast(i32x4, a[0]), __builtin_bit_cast(i32x4, a[1]), 0, 1,
+                                                 2, 3, 4, 5, 6, 7);
+        const i32x8 bv = __builtin_shufflevector(__builtin_bit_cast(i32x4, b[0]), __builtin_bit_cast(i32x4, b[1]), 0, 1,
+                                                 2, 3, 4, 5, 6, 7);
+        // formats 0/0 = FP8 e4m3 for both operands; zero scale operands select
+        // the unscaled instruction: the per-tensor FP32 scales go into alpha
+        acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(bv, av, acc, 0, 0, 0, 0, 0, 0);
+    }
+}
 
 // One k-step of MFMAs.  ZERO: the accumulators start from the constant 0
 // (the first k-step of a segment), so they need no separate clearing.
@@ -590,6 +645,314 @@ __device__ __forceinline__ void ktile_dma(Ctx<C> &cx, Frag<C> (&f)[2], typename 
     }
 }
 
+// ---------------------------------------------------------------------------
+// MAC loop of the eight-wave 256x256 tiles (PP)
+//
+// Two waves share each SIMD.  Waves 0-3 (wave row 0) and 4-7 (wave row 1) run
+// half a phase apart: while one group issues its MFMAs, the other reads its
+// next operand fragments from LDS and issues its next global -> LDS loads.
+// A k-tile is four phases of a quarter of the wave's MFMAs each; a phase
+// needs one half of A (128 rows) and one half of B (128 columns):
+//     phase 0: A0 B0    1: A0 B1    2: A1 B0    3: A1 B1
+// and reads one half-tile: A0, B1, A1 and, in phase 3, B0 of the next k-tile.
+// Half-tiles are numbered in the order they are read and loaded, B0 A0 B1 A1
+// of each k-tile: phase c reads half-tile c + 1 and issues the loads of
+// half-tile c + 7, into the buffer of half-tile c - 1.  A wave waits, at the
+// end of a phase's loads, for all but its newest five half-tiles, so a load
+// has five phases (1.25 k-tiles) to land in two k-tile buffers.
+//
+// Ordering: phase c's memory part runs in interval 2c for group 0, 2c + 1
+// for group 1, its MFMAs in the interval after; a workgroup barrier separates
+// intervals.  Half-tile c + 1 has landed for every wave by the end of its
+// phase c - 1 (interval 2c - 1 at the latest), before any wave reads it in
+// phase c.  Half-tile c - 1, overwritten from interval 2c on, was read in
+// phase c - 2, and those reads were waited for (by that phase's MFMAs, or for
+// B0 after them) in interval 2c - 2 at the latest.
+//
+// What bounds it, and what it measured (8192^3, B row-major, N(0,1) inputs,
+// one box): the two-buffer loop with one barrier per k-tile that this
+// replaces lost a fifth of its time to the fragment reads behind that barrier;
+// BF16 881 us, FP8 (four waves) 583.  Here the length of the memory part
+// decides: with the edge tests in every load BF16 took 777 us, without them
+// (WHOLE) 727 (1511 TFLOP/s), FP8 397 (2768).  The 16x16 MFMA forms draw less
+// power than the 32x32 ones, and power sets the clock: MFMAs alone from
+// registers on N(0,1) values 2064 against 1767 TFLOP/s.  On zero inputs the
+// same BF16 kernel takes 565 us; its MFMAs and barriers alone, no loads, 500.
+// Measured and dropped: two phases of twice the MFMAs (BF16 782 us, FP8 409,
+// both with the tests); loads among the MFMAs (+4 %: a load that cannot issue
+// stalls the MFMAs behind it); one barrier per phase with the next fragments
+// read a phase ahead (the registers spill); four waves of 128x128 (they
+// spill).
+// ---------------------------------------------------------------------------
+
+// Chunk swizzle of k-row p of a !KC half-tile (128 values per k-row): two
+// 16-lane groups' transpose reads, whose k-rows lie 8 (16-bit) or 32 (FP8)
+// apart, hit every bank once.
+template <int E>
+__device__ __forceinline__ int half_swizzle(int p) {
+    if constexpr (E == 2) return 4 * (p & 3) ^ 2 * ((p >> 3) & 1);
+    else return 2 * ((p >> 1) & 3) ^ ((p >> 4) & 1);
+}
+
+// One operand's two half-tiles (HR rows x BK each).  Lanes past the edge of
+// the matrix, and every lane of a k-tile past the segment's end, get an offset
+// past the resource range and deposit zeros, so the count of loads in flight
+// is constant.
+template <class C, bool KC, int HR>
+struct HalfDma {
+    static constexpr int E = C::E, VEC = C::VEC, BK = C::BK, NW = C::NW, KROW = C::KROW;
+    static constexpr int NL = HR * KROW / C::DMA_ROUND;    // loads per wave per half-tile
+    static constexpr int LPR = KROW / 16, RPB = 1024 / KROW;
+    static constexpr int CPR = HR * E / 16, KR = 1024 / (HR * E);
+    static constexpr int STEP = KC ? NW * RPB : NW * KR;   // rows (KC) or k-rows between a wave's loads
+    static constexpr uint32_t OOB = 0x80000000u;
+    const char *ub;       // the tile's first row at k = 0
+    int64_t ustep;        // bytes from one k-tile to the next
+    uint32_t ldb;         // bytes between rows (KC) or k-rows (!KC)
+    uint32_t voff[2];     // KC: {whole k-tiles, the last, partial one}; !KC: one per half
+    int pos;              // the lane's row (KC) or k-row within a load
+    int rows;             // valid rows from the tile's first one
+    int K;
+    uint32_t w1024;       // the wave's 1 KiB block of a round
+
+    __device__ __forceinline__ void init(const void *ptr, int64_t ld, int row0, int rows_total, int k, int tid) {
+        const int w = __builtin_amdgcn_readfirstlane(tid >> 6), L = tid & 63;
+        K = k;
+        w1024 = (uint32_t)w * 1024u;
+        ldb = (uint32_t)(ld * E);
+        rows = rows_total - row0;
+        if constexpr (KC) {
+            ub = (const char *)ptr + (int64_t)row0 * ld * E;
+            ustep = KROW;
+            pos = RPB * w + L / LPR;
+            const int c = (L % LPR) ^ ((pos >> 1) & 7);
+            voff[0] = pos * ldb + c * 16;
+            voff[1] = k / BK * BK + c * VEC < k ? voff[0] : OOB;
+        } else {
+            ub = (const char *)ptr + (int64_t)row0 * E;
+            ustep = (int64_t)BK * ld * E;
+            pos = w * KR + L / CPR;
+            const int c = (L % CPR) ^ half_swizzle<E>(pos);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) voff[h] = h * HR + c * VEC < rows ? pos * ldb + (h * HR * E + c * 16) : OOB;
+        }
+    }
+
+    __device__ __forceinline__ static i32x4 rsrc(uint64_t base) {
+        return i32x4{__builtin_amdgcn_readfirstlane((int)(uint32_t)base),
+                     __builtin_amdgcn_readfirstlane((int)((uint32_t)(base >> 32) & 0xffffu)), 0x7fffffff, 0x00020000};
+    }
+    // One 1 KiB load.  Issued as text: the compiler would otherwise wait,
+    // before the reads of one buffer, for loads into others (it keeps too few
+    // of them apart).
+    __device__ __forceinline__ static void dma(const i32x4 &rs, uint32_t dst, uint32_t vo, uint32_t so) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                     :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(vo), "s"(rs), "s"(__builtin_amdgcn_readfirstlane(so))
+                     : "memory", "m0");
+    }
+    __device__ __forceinline__ uint32_t dst(char *lds, int i) const {
+        return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds + i * C::DMA_ROUND + w1024;
+    }
+
+    // The wave's loads of half-tile H of k-tile kt into the buffer `lds`.
+    // WHOLE: the half-tile lies inside the matrix and `next` is its k-tile's
+    // base address.
+    template <int H, bool WHOLE = false>
+    __device__ __forceinline__ void issue(char *lds, int kt, bool live, uint64_t next = 0) const {
+        const int krem = K - kt * BK;     // > 0 when live
+        const i32x4 rs = rsrc(WHOLE ? next : (uint64_t)ub + kt * ustep);
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const uint32_t so = (KC ? H * HR + i * STEP : i * STEP) * ldb;
+            uint32_t vo = voff[KC ? 0 : H];
+            if constexpr (!WHOLE) {
+                // rows (KC) or k-rows of this load that lie inside the matrix
+                const int lim = live ? (KC ? rows - (H * HR + i * STEP) : krem - i * STEP) : 0;
+                vo = pos < lim ? (KC && krem < BK ? voff[1] : vo) : OOB;
+            }
+            dma(rs, dst(lds, i), vo, so);
+        }
+    }
+};
+
+// One 16x16 MFMA operand fragment of k-step ks from a half-tile buffer of HR
+// rows: lane l feeds row row0 + l % 16 with the k values of lane group l / 16
+// (8 of 32 for 16-bit types, 32 of 128 for FP8).  !KC: as frag_tr / frag_tr8,
+// with a lane group's transpose reads covering its own 16 rows.
+template <class C, bool KC, int HR>
+__device__ __forceinline__ void read_half_frag(u32x4 (&out)[Frag<C>::CPM], const char *op, int row0, int ks, int lane) {
+    const int g = lane >> 4, s16 = lane & 15;
+    if constexpr (KC) {
+#pragma unroll
+        for (int s = 0; s < Frag<C>::CPM; ++s)
+            out[s] = *(const u32x4 *)(op + lds_off<C::KROW>((uint32_t)(row0 + s16), (uint32_t)(ks * 4 + g + 4 * s)));
+    } else if constexpr (C::DT == Dt::F8) {
+        typedef int i32x2 __attribute__((ext_vector_type(2)));
+        // (adding 8 h or 64 to the k-row leaves its swizzle alone)
+        const int r0 = row0 + 8 * (s16 & 1), p0 = 16 * g + (s16 >> 1);
+        const char *const src = op + p0 * HR + (((r0 >> 4) ^ half_swizzle<1>(p0)) << 4) + (r0 & 15);
+        uint32_t v[8];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const i32x2 x = __builtin_amdgcn_ds_read_tr8_b64_v2i32(
+                (__attribute__((address_space(3))) i32x2 *)(src + (64 * (h >> 1) + 8 * (h & 1)) * HR));
+            v[2 * h] = (uint32_t)x[0];
+            v[2 * h + 1] = (uint32_t)x[1];
+        }
+        out[0] = u32x4{v[0], v[1], v[2], v[3]};
+        out[1] = u32x4{v[4], v[5], v[6], v[7]};
+    } else {
+        typedef short s16x4 __attribute__((ext_vector_type(4)));
+        const int r0 = row0 + 4 * (s16 & 3), p0 = 8 * g + (s16 >> 2);
+        const char *const src = op + p0 * HR * 2 + (((r0 >> 3) ^ half_swizzle<2>(p0)) << 4) + (r0 & 7) * 2;
+        u32x2 v[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            v[h] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                                                 (__attribute__((address_space(3))) s16x4 *)(src + (32 * ks + 4 * h) * HR * 2)));
+        }
+        out[0] = u32x4{v[0][0], v[0][1], v[1][0], v[1][1]};
+    }
+}
+
+template <class C>
+struct PpState {
+    static constexpr int HM = C::BM / 2, HN = C::BN / 2, FMH = C::FM / 2, FNH = C::FN / 2;
+    static constexpr int KS = Frag<C>::NSUB, CPM = Frag<C>::CPM;
+    HalfDma<C, C::AKC, HM> da;
+    HalfDma<C, C::BKC, HN> db;
+    u32x4 a[FMH][KS][CPM], b[2][FNH][KS][CPM];
+    static constexpr int NL = 2;      // loads per wave of one half-tile
+
+    __device__ __forceinline__ void read_a(const char *op, int wm, int lane) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int i = 0; i < FMH; ++i)
+                read_half_frag<C, C::AKC, HM>(a[i][ks], op, wm * (C::WTM / 2) + i * C::MT, ks, lane);
+    }
+    template <int H>
+    __device__ __forceinline__ void read_b(const char *op, int wn, int lane) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int j = 0; j < FNH; ++j)
+                read_half_frag<C, C::BKC, HN>(b[H][j][ks], op, wn * (C::WTN / 2) + j * C::MT, ks, lane);
+    }
+    template <int HA, int HB>
+    __device__ __forceinline__ void mfma(typename C::Frag (&acc)[C::FM][C::FN]) const {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int i = 0; i < FMH; ++i)
+#pragma unroll
+                for (int j = 0; j < FNH; ++j)
+                    mfma16<C>(acc[HA * FMH + i][HB * FNH + j], a[i][ks], b[HB][j][ks]);
+    }
+};
+
+// a workgroup barrier that neither the compiler nor the scheduler moves
+// anything across (it waits for nothing by itself)
+__device__ __forceinline__ void plain_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
+
+// every LDS access of this wave is done
+__device__ __forceinline__ void wait_lds() {
+    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+    asm volatile("" ::: "memory");
+}
+
+// k-tile t in stage S.  WHOLE: the next two k-tiles lie inside the segment
+// and the matrices, so their loads need no tests (abase, bbase: the addresses
+// of k-tiles t + 1 of A and t + 2 of B, advanced)
+template <class C, int S, bool WHOLE>
+__device__ __forceinline__ void ktile_pp(PpState<C> &st, typename C::Frag (&acc)[C::FM][C::FN], const LdsBufs &bufs,
+                                         int t, int t1, int wm, int wn, int lane, uint64_t &abase, uint64_t &bbase) {
+    char *const A0 = bufs.template get<4 * S>(), *const A1 = bufs.template get<4 * S + 1>();
+    char *const B0 = bufs.template get<4 * S + 2>(), *const B1 = bufs.template get<4 * S + 3>();
+    char *const A1n = bufs.template get<4 * (1 - S) + 1>();
+    const char *const B0n = bufs.template get<4 * (1 - S) + 2>();
+    const bool live1 = t + 1 < t1, live2 = t + 2 < t1;
+    static_for<4>([&](auto pp) {
+        constexpr int p = decltype(pp)::value;
+        if constexpr (p == 0) st.read_a(A0, wm, lane);
+        else if constexpr (p == 1) st.template read_b<1>(B1, wn, lane);
+        else if constexpr (p == 2) st.read_a(A1, wm, lane);
+        else st.template read_b<0>(B0n, wn, lane);
+        if constexpr (p == 0) {
+            st.da.template issue<1, WHOLE>(A1n, t + 1, live1, abase);
+            abase += st.da.ustep;
+        } else if constexpr (p == 1) {
+            st.db.template issue<0, WHOLE>(B0, t + 2, live2, bbase);
+        } else if constexpr (p == 2) {
+            st.da.template issue<0, WHOLE>(A0, t + 2, live2, abase);
+        } else {
+            st.db.template issue<1, WHOLE>(B1, t + 2, live2, bbase);
+            bbase += st.db.ustep;
+        }
+        // all but the newest five half-tiles: half-tile 4 t + p + 2 has landed
+        wait_dma_but<5 * PpState<C>::NL>();
+        plain_barrier();
+        __builtin_amdgcn_s_setprio(1);
+        st.template mfma<p / 2, p % 2>(acc);
+        __builtin_amdgcn_s_setprio(0);
+        if constexpr (p == 3) wait_lds();    // B0's reads: no MFMA of this phase has waited for them
+        plain_barrier();
+    });
+}
+
+template <class C>
+__device__ __forceinline__ void mac_loop_pp(const Problem &P, int tm, int tn, int it0, int it1,
+                                            typename C::Frag (&acc)[C::FM][C::FN], const LdsBufs &bufs, int tid) {
+    const int lane = tid & 63, wave = tid >> 6;
+    const int uw = __builtin_amdgcn_readfirstlane(wave), wm = uw / C::WGN, wn = uw % C::WGN;
+    PpState<C> st;
+    st.da.init(P.A, P.lda, tm * C::BM, P.m, P.k, tid);
+    st.db.init(P.B, P.ldb, tn * C::BN, P.n, P.k, tid);
+    static_for<2>([&](auto ss) {
+        constexpr int s = decltype(ss)::value;
+        const bool live = it0 + s < it1;
+        st.db.template issue<0>(bufs.template get<4 * s + 2>(), it0 + s, live);
+        st.da.template issue<0>(bufs.template get<4 * s>(), it0 + s, live);
+        st.db.template issue<1>(bufs.template get<4 * s + 3>(), it0 + s, live);
+        if constexpr (s == 0) st.da.template issue<1>(bufs.template get<4 * s + 1>(), it0 + s, live);
+    });
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j) acc[i][j] = typename C::Frag{};
+    wait_dma_but<5 * PpState<C>::NL>();      // B0 and A0 of the first k-tile
+    plain_barrier();
+    st.template read_b<0>(bufs.b2, wn, lane);
+    wait_lds();
+    if (wm == 1) plain_barrier();            // half a phase behind
+    int t = it0;
+    uint64_t ab = 0, bb = 0;
+    if ((tm + 1) * C::BM <= P.m && (tn + 1) * C::BN <= P.n) {
+        const int full = P.k / C::BK < it1 ? P.k / C::BK : it1;
+        ab = (uint64_t)st.da.ub + (it0 + 1) * st.da.ustep;
+        bb = (uint64_t)st.db.ub + (it0 + 2) * st.db.ustep;
+        for (; t + 3 < full; t += 2) {
+            ktile_pp<C, 0, true>(st, acc, bufs, t, it1, wm, wn, lane, ab, bb);
+            ktile_pp<C, 1, true>(st, acc, bufs, t + 1, it1, wm, wn, lane, ab, bb);
+        }
+    }
+    for (; t < it1; t += 2) {
+        ktile_pp<C, 0, false>(st, acc, bufs, t, it1, wm, wn, lane, ab, bb);
+        if (t + 1 < it1) ktile_pp<C, 1, false>(st, acc, bufs, t + 1, it1, wm, wn, lane, ab, bb);
+    }
+    if (wm == 0) plain_barrier();
+    // the loads past the segment's end still write into the buffers, which
+    // the epilogue uses next
+    wait_dma();
+    __syncthreads();
+}
+
 template <class C>
 __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int it0, int it1,
                                          typename C::Frag (&acc)[C::FM][C::FN], const LdsBufs &bufs,
@@ -663,10 +1026,10 @@ __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int i
 // accumulator <-> (row, col) and the epilogue
 // ---------------------------------------------------------------------------
 // Output layout of a fragment.
-// 32x32 blocks (f16/bf16/f8): the MFMAs compute D = B_frag * A_frag, the
-// transposed block, so lane l holds C row (l % 32) of the block and, in
-// accumulator register 4g+e, column 8g + 4(l / 32) + e: four consecutive
-// columns per group g, stored as one vector.
+// 32x32 and 16x16 blocks of f16/bf16/f8: the MFMAs compute D = B_frag *
+// A_frag, the transposed block, so lane l holds C row (l % MT) of the block
+// and, in accumulator register 4g+e, column 8g + 4(l / MT) + e: four
+// consecutive columns per group g (16x16: one group), stored as one vector.
 // 16x16 f64 blocks: D = A_frag * B_frag; lane l holds column (l % 16) and,
 // in register r, row 4r + (l / 16).
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
@@ -769,7 +1132,9 @@ __device__ __forceinline__ typename C::Frag load_partial_frag(const char *slot, 
     for (int s = 0; s < PL::CPF; ++s)
         c[s] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (uint32_t)PL::off(i, j, s, tid),
                                                                              0, CPOL_DEVICE));
-    if constexpr (PL::PER == 4) {
+    if constexpr (PL::CPF == 1) {
+        return __builtin_bit_cast(f32x4, c[0]);
+    } else if constexpr (PL::PER == 4) {
         const f32x8 lo = __builtin_shufflevector(__builtin_bit_cast(f32x4, c[0]), __builtin_bit_cast(f32x4, c[1]), 0,
                                                  1, 2, 3, 4, 5, 6, 7);
         const f32x8 hi = __builtin_shufflevector(__builtin_bit_cast(f32x4, c[2]), __builtin_bit_cast(f32x4, c[3]), 0,
@@ -817,14 +1182,21 @@ struct FixStage {
     static constexpr int ROWS_PH = C::FM / PH;                        // fragment rows per phase
     static constexpr int RB = C::DMA_ROUND;                           // bytes of one chunk of every thread
     static_assert(H * RB <= C::STAGE && C::FM % PH == 0 && VPH % 2 == 0, "fixup staging fits the LDS");
+    static_assert(!C::PP || C::LDS_OBJ % RB == 0, "whole chunks per half-tile buffer");
+
+    // LDS address of chunk u of a phase (u is a constant after unrolling)
+    __device__ static __forceinline__ char *at(const LdsBufs &bufs, int u) {
+        if constexpr (C::PP) return bufs.template at<8>(u * RB / C::LDS_OBJ) + u * RB % C::LDS_OBJ;
+        else return (u < H ? bufs.b0 : bufs.b1) + (u % H) * RB;
+    }
 
     // stage chunks [ph*VPH, (ph+1)*VPH) of the slot
-    __device__ static __forceinline__ void issue(const char *slot, char *lds0, char *lds1, int ph, int tid) {
+    __device__ static __forceinline__ void issue(const char *slot, const LdsBufs &bufs, int ph, int tid) {
         const __amdgpu_buffer_rsrc_t rs = slot_rsrc(slot, C::SLOT_BYTES);
         const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
         for (int u = 0; u < VPH; ++u) {
-            char *dst = (u < H ? lds0 : lds1) + (u % H) * RB + w * 1024;
+            char *dst = at(bufs, u) + w * 1024;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)dst, 16,
                                                      (uint32_t)tid * 16u, (uint32_t)((ph * VPH + u) * RB), 0,
                                                      CPOL_DEVICE);
@@ -832,16 +1204,17 @@ struct FixStage {
     }
 
     // fragment (i, j) of the staged slot
-    __device__ static __forceinline__ typename C::Frag frag(const char *lds0, const char *lds1, int i, int j,
-                                                            int tid) {
+    __device__ static __forceinline__ typename C::Frag frag(const LdsBufs &bufs, int i, int j, int tid) {
         using PL = PartialLayout<C>;
         u32x4 c[PL::CPF];
 #pragma unroll
         for (int s = 0; s < PL::CPF; ++s) {
             const int u = (i * C::FN + j) * PL::CPF + s - (i / ROWS_PH) * VPH;
-            c[s] = *(const u32x4 *)((u < H ? lds0 : lds1) + (u % H) * RB + tid * 16);
+            c[s] = *(const u32x4 *)(at(bufs, u) + tid * 16);
         }
-        if constexpr (PL::PER == 4) {
+        if constexpr (PL::CPF == 1) {
+            return __builtin_bit_cast(f32x4, c[0]);
+        } else if constexpr (PL::PER == 4) {
             const f32x8 lo = __builtin_shufflevector(__builtin_bit_cast(f32x4, c[0]), __builtin_bit_cast(f32x4, c[1]),
                                                      0, 1, 2, 3, 4, 5, 6, 7);
             const f32x8 hi = __builtin_shufflevector(__builtin_bit_cast(f32x4, c[2]), __builtin_bit_cast(f32x4, c[3]),
@@ -860,28 +1233,24 @@ struct FixStage {
 // to the start of the epilogue (which exhausts the VGPRs).
 template <class C>
 __device__ __forceinline__ typename C::Frag fix_frag(const typename C::Frag &a, const char *slots, int p0, int p1,
-                                                     const char *lds0, const char *lds1, int i, int j, int tid) {
-    if constexpr (!C::FIX_LDS) {
-        return add_peers<C>(a, slots, p0, p1, i, j, tid);
-    } else {
-        typename C::Frag v = a;
-        asm volatile("" : "+v"(v));
-        if (p0 <= p1) {
-            v = v + FixStage<C>::frag(lds0, lds1, i, j, tid);
-            v = add_peers<C>(v, slots, p0 + 1, p1, i, j, tid);
-        }
-        return v;
+                                                     const LdsBufs &bufs, int i, int j, int tid) {
+    typename C::Frag v = a;
+    asm volatile("" : "+v"(v));
+    if (p0 <= p1) {
+        v = v + FixStage<C>::frag(bufs, i, j, tid);
+        v = add_peers<C>(v, slots, p0 + 1, p1, i, j, tid);
     }
+    return v;
 }
 
 // Phase boundary of the staged fixup: stage the phase's chunks of the first
 // peer (after this wave's reads of the previous phase) and wait for them.
 template <class C>
-__device__ __forceinline__ void fix_phase(bool staged, const char *slots, int p0, char *lds0, char *lds1, int i,
+__device__ __forceinline__ void fix_phase(bool staged, const char *slots, int p0, const LdsBufs &bufs, int i,
                                           int tid) {
-    if (C::FIX_LDS && staged && i % FixStage<C>::ROWS_PH == 0) {
+    if (staged && i % FixStage<C>::ROWS_PH == 0) {
         if (i > 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        FixStage<C>::issue(slots + (int64_t)p0 * C::SLOT_BYTES, lds0, lds1, i / FixStage<C>::ROWS_PH, tid);
+        FixStage<C>::issue(slots + (int64_t)p0 * C::SLOT_BYTES, bufs, i / FixStage<C>::ROWS_PH, tid);
         wait_dma();
     }
 }
@@ -894,42 +1263,51 @@ __device__ __forceinline__ void fix_phase(bool staged, const char *slots, int p0
 // 1 KiB of consecutive bytes (512 with a 16-bit C), a few whole 128-byte
 // lines, which makes small-k GEMMs (output-write bound) several times
 // cheaper.  The arithmetic per element is that of store_tile_t: alpha * acc,
-// then + beta * C, rounded once.  One band of 2 x 32 rows (32 rows per wave
-// row) per fragment row i; each padded LDS row (BN floats + 16 bytes) starts
+// then + beta * C, rounded once.  Bands of 2 x 32 rows (32 per wave row); each padded LDS row (BN floats + 16 bytes) starts
 // 4 banks after the previous one, so the 32 rows of a fragment write land in
-// distinct banks.  Rows and columns past the edge of C are not stored.
+// distinct banks (PP: eight rows per half-tile buffer, the rows of buffer b
+// another 32 (b % 4) banks on).  Rows and columns past the edge of C are not
+// stored.
 template <class C, int CT>
 __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn,
-                                                const typename C::Frag (&acc)[C::FM][C::FN], int tid, char *lds0,
-                                                char *lds1, bool interior) {
+                                                const typename C::Frag (&acc)[C::FM][C::FN], int tid,
+                                                const LdsBufs &bufs, bool interior) {
     using Acc = typename C::Acc;
     constexpr int EB = CBytes<CT>::v;
     constexpr int G = C::FRAG_N / 4;                  // column groups per fragment
     constexpr int RS = C::BN * 4 + 16;                // padded LDS row
     constexpr int Q = C::BN / 4;                      // 16-byte chunks per row
-    constexpr int NCH = C::WGM * C::MT * Q / C::THREADS;   // chunks per thread per band
-    static_assert(C::MT == 32 && C::WGM == 2 && C::MT * RS <= C::STAGE, "a band's half fits one k-tile buffer");
-    static_assert((C::WGM * C::MT * Q) % C::THREADS == 0, "whole chunks per thread");
+    constexpr int BR = 32, FB = BR / C::MT;           // band rows per wave row, in FB fragment rows
+    constexpr int NCH = C::WGM * BR * Q / C::THREADS; // chunks per thread per band
+    static_assert(C::WGM == 2 && (C::PP ? 8 * RS + 384 <= C::LDS_OBJ && C::THREADS == 8 * Q : BR * RS <= C::STAGE),
+                  "a band fits the k-tile buffers");
+    static_assert((C::WGM * BR * Q) % C::THREADS == 0, "whole chunks per thread");
     const int lane = tid & 63, wave = tid >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
-    char *const half = wm == 0 ? lds0 : lds1;
-    const int wr = (lane % C::MT) * RS + (wn * C::WTN + 4 * (lane / C::MT)) * 4;
     const Acc alpha = (Acc)P.alpha, beta = (Acc)P.beta;
     const bool rd = P.beta != 0.0;
-    static_for<C::FM>([&](auto ii) {
-        constexpr int i = decltype(ii)::value;
+    static_for<C::FM / FB>([&](auto ii) {
+        constexpr int i = decltype(ii)::value * FB;   // the band's first fragment row
         __syncthreads();                              // LDS free: MAC-loop reads, previous band
 #pragma unroll
-        for (int j = 0; j < C::FN; ++j) {
-            // an opaque copy where it is used, as in fix_frag: the copies of
-            // all fragments are not hoisted out of the accumulator registers
-            typename C::Frag f = acc[i][j];
-            asm volatile("" : "+v"(f));
+        for (int fb = 0; fb < FB; ++fb) {
+            const int lr = fb * C::MT + lane % C::MT;
+            char *const row = C::PP ? bufs.template at<8>(wm * 4 + lr / 8) + lr % 8 * RS + lr / 8 * 128
+                                    : (wm == 0 ? bufs.b0 : bufs.b1) + lr * RS;
+            char *const wr = row + (C::fcol(wn, 0) + 4 * (lane / C::MT)) * 4;
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                f32x4 v;
+            for (int j = 0; j < C::FN; ++j) {
+                // an opaque copy where it is used, as in fix_frag: the copies
+                // of all fragments are not hoisted out of the accumulator
+                // registers
+                typename C::Frag f = acc[i + fb][j];
+                asm volatile("" : "+v"(f));
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = alpha * f[4 * g + e];
-                *(f32x4 *)(half + wr + (j * C::MT + 8 * g) * 4) = v;
+                for (int g = 0; g < G; ++g) {
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = alpha * f[4 * g + e];
+                    *(f32x4 *)(wr + (C::fcol(0, j) + 8 * g) * 4) = v;
+                }
             }
         }
         __syncthreads();
@@ -937,8 +1315,9 @@ __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn
         for (int u = 0; u < NCH; ++u) {
             const int c = tid + u * C::THREADS;
             const int br = c / Q, c4 = c % Q;         // band row, chunk in the row
-            const f32x4 v = *(const f32x4 *)((br < C::MT ? lds0 : lds1) + (br % C::MT) * RS + c4 * 16);
-            const int row = tm * C::BM + (br / C::MT) * C::WTM + i * C::MT + br % C::MT;
+            const f32x4 v = *(const f32x4 *)(C::PP ? bufs.template at<8>(u) + wave * RS + u % 4 * 128 + lane * 16
+                                                   : (br < BR ? bufs.b0 : bufs.b1) + (br % BR) * RS + c4 * 16);
+            const int row = tm * C::BM + C::frow(br / BR, i) + br % BR;
             const int col = tn * C::BN + 4 * c4;
             const Acc a[4] = {v[0], v[1], v[2], v[3]};
             char *const q = (char *)P.C + ((int64_t)row * P.ldc + col) * EB;
@@ -969,7 +1348,7 @@ __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn
 template <class C, int CT>
 __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
                                              const typename C::Frag (&acc)[C::FM][C::FN], int tid,
-                                             const char *slots, int p0, int p1, char *lds0, char *lds1) {
+                                             const char *slots, int p0, int p1, const LdsBufs &bufs) {
     using Acc = typename C::Acc;
     constexpr int EB = CBytes<CT>::v;
     constexpr int G = C::FRAG_N / 4;                 // column groups per fragment
@@ -978,7 +1357,7 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
     const bool rd = P.beta != 0.0;
     const bool interior = (tm + 1) * C::BM <= P.m && (tn + 1) * C::BN <= P.n;
     const bool fast = P.c_vec && interior;
-    if constexpr (C::MT == 16) {
+    if constexpr (C::DT == Dt::F64) {
         // f64: one element per store; a lane group of 16 writes 128
         // consecutive bytes of one row
         const int r0 = tm * C::BM + wm * C::WTM + (lane >> 4);
@@ -986,8 +1365,8 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
         const bool staged = p0 <= p1;
         static_for<C::FM * C::FN>([&](auto ij) {
             constexpr int i = decltype(ij)::value / C::FN, j = decltype(ij)::value % C::FN;
-            if constexpr (j == 0) fix_phase<C>(staged, slots, p0, lds0, lds1, i, tid);
-            const typename C::Frag v = fix_frag<C>(acc[i][j], slots, p0, p1, lds0, lds1, i, j, tid);
+            if constexpr (j == 0) fix_phase<C>(staged, slots, p0, bufs, i, tid);
+            const typename C::Frag v = fix_frag<C>(acc[i][j], slots, p0, p1, bufs, i, j, tid);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = r0 + i * 16 + 4 * r, col = c0 + j * 16;
@@ -1005,27 +1384,27 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
     // (16-bit inputs only, from the 128x128 tile on: the staging's registers
     // would cost the 64x64 Stream-K kernel a wave per SIMD, and with it the
     // FP8 kernels' MAC loops measured 3 % slower at large k)
-    if constexpr (C::MT == 32 && C::BM >= 128 && C::DT != Dt::F8) {
+    if constexpr (C::BM >= 128 && (C::DT != Dt::F8 || C::PP)) {
         if (P.c_vec && p0 > p1) {
             // whole rows through the LDS, edge tiles included (the flags are
             // uniform over the workgroup)
-            store_tile_rows<C, CT>(P, tm, tn, acc, tid, lds0, lds1, interior);
+            store_tile_rows<C, CT>(P, tm, tn, acc, tid, bufs, interior);
             return;
         }
     }
-    const int rowl = tm * C::BM + wm * C::WTM + (lane % C::MT);
-    const int coll = tn * C::BN + wn * C::WTN + 4 * (lane / C::MT);
+    const int rowl = tm * C::BM + C::frow(wm, 0) + (lane % C::MT);
+    const int coll = tn * C::BN + C::fcol(wn, 0) + 4 * (lane / C::MT);
     const bool staged = p0 <= p1;
     static_for<C::FM * C::FN>([&](auto ij) {
         constexpr int i = decltype(ij)::value / C::FN, j = decltype(ij)::value % C::FN;
-        if constexpr (j == 0) fix_phase<C>(staged, slots, p0, lds0, lds1, i, tid);
-        const int row = rowl + i * C::MT;
+        if constexpr (j == 0) fix_phase<C>(staged, slots, p0, bufs, i, tid);
+        const int row = rowl + C::frow(0, i);
         char *rp = (char *)P.C + ((int64_t)row * P.ldc + coll) * EB;
         {
-            const typename C::Frag f = fix_frag<C>(acc[i][j], slots, p0, p1, lds0, lds1, i, j, tid);
+            const typename C::Frag f = fix_frag<C>(acc[i][j], slots, p0, p1, bufs, i, j, tid);
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const int co = j * C::MT + 8 * g;         // column offset from coll
+                const int co = C::fcol(0, j) + 8 * g;     // column offset from coll
                 Acc v[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = alpha * f[4 * g + e];
@@ -1051,19 +1430,19 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
 template <class C>
 __device__ __forceinline__ void store_tile(const Problem &P, int tm, int tn,
                                            const typename C::Frag (&acc)[C::FM][C::FN], int tid,
-                                           const char *slots, int p0, int p1, char *lds0, char *lds1) {
+                                           const char *slots, int p0, int p1, const LdsBufs &bufs) {
     if constexpr (C::DT == Dt::F64) {
-        store_tile_t<C, SK_F64>(P, tm, tn, acc, tid, slots, p0, p1, lds0, lds1);
+        store_tile_t<C, SK_F64>(P, tm, tn, acc, tid, slots, p0, p1, bufs);
     } else {
         switch (P.c_type) {
-        case SK_F32: store_tile_t<C, SK_F32>(P, tm, tn, acc, tid, slots, p0, p1, lds0, lds1); break;
-        case SK_F16: store_tile_t<C, SK_F16>(P, tm, tn, acc, tid, slots, p0, p1, lds0, lds1); break;
-        default: store_tile_t<C, SK_BF16>(P, tm, tn, acc, tid, slots, p0, p1, lds0, lds1); break;
+        case SK_F32: store_tile_t<C, SK_F32>(P, tm, tn, acc, tid, slots, p0, p1, bufs); break;
+        case SK_F16: store_tile_t<C, SK_F16>(P, tm, tn, acc, tid, slots, p0, p1, bufs); break;
+        default: store_tile_t<C, SK_BF16>(P, tm, tn, acc, tid, slots, p0, p1, bufs); break;
         }
     }
     // the staged fixup used this wave's LDS regions: keep the next unit's
     // loads out until every wave is done with them
-    if (C::FIX_LDS && p0 <= p1) __syncthreads();
+    if (p0 <= p1) __syncthreads();
 }
 
 template <class C>
@@ -1173,12 +1552,11 @@ template <class C>
 struct Spread {
     static constexpr int N = C::SLOT_BYTES / 16;                 // chunks per tile
     static constexpr int LDS_CHUNKS = C::NSTAGE * C::STAGE / 16;  // staging capacity
-    static constexpr int BLK_PER_BUF = C::STAGE / 1024;           // 1 KiB DMA blocks per buffer
-    static_assert(C::STAGE % 1024 == 0, "whole DMA blocks per buffer");
+    static constexpr int BLK_PER_BUF = C::LDS_OBJ / 1024;         // 1 KiB DMA blocks per buffer
+    static_assert(C::LDS_OBJ % 1024 == 0, "whole DMA blocks per buffer");
 
-    __device__ static __forceinline__ char *blk(LdsBufs b, int i) {
-        const int u = i / BLK_PER_BUF, o = (i % BLK_PER_BUF) * 1024;
-        return (u == 0 ? b.b0 : u == 1 ? b.b1 : b.b2) + o;
+    __device__ static __forceinline__ char *blk(const LdsBufs &b, int i) {
+        return b.template at<C::PP ? 8 : C::NSTAGE>(i / BLK_PER_BUF) + (i % BLK_PER_BUF) * 1024;
     }
 
     // Elements of chunk c (16 bytes of the thread-fragment order) of tile
@@ -1193,7 +1571,7 @@ struct Spread {
         const int lane = t & 63, wave = t >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
         const Acc alpha = (Acc)P.alpha, beta = (Acc)P.beta;
         const bool rd = P.beta != 0.0;
-        if constexpr (C::MT == 16) {
+        if constexpr (C::DT == Dt::F64) {
             // FP64: the chunk holds rows 4(2 sc) + lane/16 and 4(2 sc + 1) + lane/16 of one column
             const f64x2 v = __builtin_bit_cast(f64x2, raw);
             const int col = tn * C::BN + wn * C::WTN + fj * 16 + (lane & 15);
@@ -1210,8 +1588,8 @@ struct Spread {
         } else {
             // 32x32 blocks: four consecutive columns of one row
             const f32x4 v = __builtin_bit_cast(f32x4, raw);
-            const int row = tm * C::BM + wm * C::WTM + fi * C::MT + (lane % C::MT);
-            const int col = tn * C::BN + wn * C::WTN + fj * C::MT + 8 * sc + 4 * (lane / C::MT);
+            const int row = tm * C::BM + C::frow(wm, fi) + (lane % C::MT);
+            const int col = tn * C::BN + C::fcol(wn, fj) + 8 * sc + 4 * (lane / C::MT);
             char *rp = (char *)P.C + ((int64_t)row * P.ldc + col) * EB;
             Acc a[4];
 #pragma unroll
@@ -1245,14 +1623,14 @@ struct Spread {
         const int sc = vi % PL::CPF, fij = vi / PL::CPF, fi = fij / C::FN, fj = fij % C::FN;
         const int lane = t & 63, wave = t >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
         int row, col;
-        if constexpr (C::MT == 16) {
+        if constexpr (C::DT == Dt::F64) {
             // FP64: the chunk holds rows 4(2 sc) + lane/16 and 4(2 sc + 1) + lane/16 of one column
             row = tm * C::BM + wm * C::WTM + fi * 16 + 4 * (2 * sc + e) + (lane >> 4);
             col = tn * C::BN + wn * C::WTN + fj * 16 + (lane & 15);
         } else {
             // 32x32 blocks: four consecutive columns of one row
-            row = tm * C::BM + wm * C::WTM + fi * C::MT + (lane % C::MT);
-            col = tn * C::BN + wn * C::WTN + fj * C::MT + 8 * sc + 4 * (lane / C::MT) + e;
+            row = tm * C::BM + C::frow(wm, fi) + (lane % C::MT);
+            col = tn * C::BN + C::fcol(wn, fj) + 8 * sc + 4 * (lane / C::MT) + e;
         }
         if (row < P.m && col < P.n) {
             char *q = (char *)P.C + ((int64_t)row * P.ldc + col) * EB;
@@ -1264,7 +1642,7 @@ struct Spread {
 
     template <int CT>
     __device__ static __forceinline__ void reduce_t(const Params &p, const Problem &P, int tm, int tn, int f,
-                                                    int l, int x, LdsBufs bufs, int tid) {
+                                                    int l, int x, const LdsBufs &bufs, int tid) {
         const int s = l - f + 1, i = x - f;
         const int c0 = (int)((int64_t)N * i / s), c1 = (int)((int64_t)N * (i + 1) / s);
         // chunks per pass: all s contributors' copies of them fit the LDS
@@ -1342,7 +1720,7 @@ struct Spread {
     }
 
     __device__ static __forceinline__ void reduce(const Params &p, const Problem &P, int tm, int tn, int f, int l,
-                                                  int x, LdsBufs bufs, int tid) {
+                                                  int x, const LdsBufs &bufs, int tid) {
         if constexpr (C::DT == Dt::F64) {
             reduce_t<SK_F64>(p, P, tm, tn, f, l, x, bufs, tid);
         } else {
@@ -1483,13 +1861,18 @@ struct DpQueue {
 template <class C, bool DP_ONLY>
 __device__ __forceinline__ void sk_body(const Params &p) {
     // the k-tile buffers of the MAC loop
-    __shared__ __attribute__((aligned(16))) char lds0[C::STAGE];
-    __shared__ __attribute__((aligned(16))) char lds1[C::STAGE];
-    __shared__ __attribute__((aligned(16))) char lds2[C::NSTAGE >= 3 ? C::STAGE : 16];
-    __shared__ __attribute__((aligned(16))) char lds3[C::NSTAGE >= 4 ? C::STAGE : 16];
+    constexpr int NOBJ = C::PP ? 8 : C::NSTAGE, OBJ = C::LDS_OBJ;
+    __shared__ __attribute__((aligned(16))) char lds0[OBJ];
+    __shared__ __attribute__((aligned(16))) char lds1[OBJ];
+    __shared__ __attribute__((aligned(16))) char lds2[NOBJ > 2 ? OBJ : 16];
+    __shared__ __attribute__((aligned(16))) char lds3[NOBJ > 3 ? OBJ : 16];
+    __shared__ __attribute__((aligned(16))) char lds4[NOBJ > 4 ? OBJ : 16];
+    __shared__ __attribute__((aligned(16))) char lds5[NOBJ > 5 ? OBJ : 16];
+    __shared__ __attribute__((aligned(16))) char lds6[NOBJ > 6 ? OBJ : 16];
+    __shared__ __attribute__((aligned(16))) char lds7[NOBJ > 7 ? OBJ : 16];
     __shared__ int next_dp;     // the next queued data-parallel tile, for all waves
     __shared__ int dp_queue[2]; // DpQueue state (thread 0 only)
-    const LdsBufs bufs{lds0, lds1, lds2, lds3};
+    const LdsBufs bufs{lds0, lds1, lds2, lds3, lds4, lds5, lds6, lds7};
     const int tid0 = threadIdx.x;
     const int b = blockIdx.x;
     int x = b;
@@ -1594,7 +1977,8 @@ __device__ __forceinline__ void sk_body(const Params &p) {
         int tid = tid0;
         asm volatile("" : "+v"(tid));
         typename C::Frag acc[C::FM][C::FN];
-        mac_loop<C>(P, tm, tn, k0, k1, acc, bufs, tid);
+        if constexpr (C::PP) mac_loop_pp<C>(P, tm, tn, k0, k1, acc, bufs, tid);
+        else mac_loop<C>(P, tm, tn, k0, k1, acc, bufs, tid);
         const int last = ended ? -1 : owner_of(t1 - 1);
         if (!started) {
             // the first segment of this range: partial slot and flag x
@@ -1622,7 +2006,7 @@ __device__ __forceinline__ void sk_body(const Params &p) {
         if (!ended) wait_flags(p.flags, x + 1, last, -1, x + 1, epoch, p.err, p.wait_ticks, tid);
         // peers' partial tiles are added in ascending slot order inside the
         // epilogue, fragment by fragment
-        store_tile<C>(P, tm, tn, acc, tid, (const char *)p.partials, x + 1, last, lds0, lds1);
+        store_tile<C>(P, tm, tn, acc, tid, (const char *)p.partials, x + 1, last, bufs);
         trace_rec(p, x, seq++, tile, k0, k1, dp_now ? ROLE_DP : (ended ? ROLE_FULL : ROLE_OWNER), last, 0,
                   tid);
         if (dp_now && dyn) {
