@@ -34,8 +34,8 @@ def unit(dt, enum, tile, lay, akc, bkc, nw=4):
 
 namespace sk {{
 KernelEntry pick_{dt}_{tile}_{lay}(const KernelKey &k) {{
-    return k.grouped ? entry<Dt::{enum}, {tile}, {tile}, {akc}, {bkc}, true{w}>(k.dp_only)
-                     : entry<Dt::{enum}, {tile}, {tile}, {akc}, {bkc}, false{w}>(k.dp_only);
+    return k.grouped ? entry<Dt::{enum}, {tile}, {tile}, {akc}, {bkc}, true{w}>(k)
+                     : entry<Dt::{enum}, {tile}, {tile}, {akc}, {bkc}, false{w}>(k);
 }}
 }}  // namespace sk
 """

@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_bf16_256_nn(const KernelKey &k) {
-    return k.grouped ? entry<Dt::BF16, 256, 256, false, false, true, 8>(k.dp_only)
-                     : entry<Dt::BF16, 256, 256, false, false, false, 8>(k.dp_only);
+    return k.grouped ? entry<Dt::BF16, 256, 256, false, false, true, 8>(k)
+                     : entry<Dt::BF16, 256, 256, false, false, false, 8>(k);
 }
 }  // namespace sk

@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_bf16_64_kn(const KernelKey &k) {
-    return k.grouped ? entry<Dt::BF16, 64, 64, true, false, true>(k.dp_only)
-                     : entry<Dt::BF16, 64, 64, true, false, false>(k.dp_only);
+    return k.grouped ? entry<Dt::BF16, 64, 64, true, false, true>(k)
+                     : entry<Dt::BF16, 64, 64, true, false, false>(k);
 }
 }  // namespace sk

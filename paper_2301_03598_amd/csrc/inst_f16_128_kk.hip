@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_f16_128_kk(const KernelKey &k) {
-    return k.grouped ? entry<Dt::F16, 128, 128, true, true, true>(k.dp_only)
-                     : entry<Dt::F16, 128, 128, true, true, false>(k.dp_only);
+    return k.grouped ? entry<Dt::F16, 128, 128, true, true, true>(k)
+                     : entry<Dt::F16, 128, 128, true, true, false>(k);
 }
 }  // namespace sk

@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_f16_256_kn(const KernelKey &k) {
-    return k.grouped ? entry<Dt::F16, 256, 256, true, false, true, 8>(k.dp_only)
-                     : entry<Dt::F16, 256, 256, true, false, false, 8>(k.dp_only);
+    return k.grouped ? entry<Dt::F16, 256, 256, true, false, true, 8>(k)
+                     : entry<Dt::F16, 256, 256, true, false, false, 8>(k);
 }
 }  // namespace sk

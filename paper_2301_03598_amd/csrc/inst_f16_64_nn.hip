@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_f16_64_nn(const KernelKey &k) {
-    return k.grouped ? entry<Dt::F16, 64, 64, false, false, true>(k.dp_only)
-                     : entry<Dt::F16, 64, 64, false, false, false>(k.dp_only);
+    return k.grouped ? entry<Dt::F16, 64, 64, false, false, true>(k)
+                     : entry<Dt::F16, 64, 64, false, false, false>(k);
 }
 }  // namespace sk

@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_f64_128_kn(const KernelKey &k) {
-    return k.grouped ? entry<Dt::F64, 128, 128, true, false, true>(k.dp_only)
-                     : entry<Dt::F64, 128, 128, true, false, false>(k.dp_only);
+    return k.grouped ? entry<Dt::F64, 128, 128, true, false, true>(k)
+                     : entry<Dt::F64, 128, 128, true, false, false>(k);
 }
 }  // namespace sk

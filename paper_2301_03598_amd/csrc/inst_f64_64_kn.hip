@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_f64_64_kn(const KernelKey &k) {
-    return k.grouped ? entry<Dt::F64, 64, 64, true, false, true>(k.dp_only)
-                     : entry<Dt::F64, 64, 64, true, false, false>(k.dp_only);
+    return k.grouped ? entry<Dt::F64, 64, 64, true, false, true>(k)
+                     : entry<Dt::F64, 64, 64, true, false, false>(k);
 }
 }  // namespace sk

@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_f8_128_kk(const KernelKey &k) {
-    return k.grouped ? entry<Dt::F8, 128, 128, true, true, true>(k.dp_only)
-                     : entry<Dt::F8, 128, 128, true, true, false>(k.dp_only);
+    return k.grouped ? entry<Dt::F8, 128, 128, true, true, true>(k)
+                     : entry<Dt::F8, 128, 128, true, true, false>(k);
 }
 }  // namespace sk

@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_f8_256_nk(const KernelKey &k) {
-    return k.grouped ? entry<Dt::F8, 256, 256, false, true, true, 8>(k.dp_only)
-                     : entry<Dt::F8, 256, 256, false, true, false, 8>(k.dp_only);
+    return k.grouped ? entry<Dt::F8, 256, 256, false, true, true, 8>(k)
+                     : entry<Dt::F8, 256, 256, false, true, false, 8>(k);
 }
 }  // namespace sk

@@ -4,7 +4,7 @@
 
 namespace sk {
 KernelEntry pick_f8_64_nn(const KernelKey &k) {
-    return k.grouped ? entry<Dt::F8, 64, 64, false, false, true>(k.dp_only)
-                     : entry<Dt::F8, 64, 64, false, false, false>(k.dp_only);
+    return k.grouped ? entry<Dt::F8, 64, 64, false, false, true>(k)
+                     : entry<Dt::F8, 64, 64, false, false, false>(k);
 }
 }  // namespace sk

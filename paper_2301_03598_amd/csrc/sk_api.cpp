@@ -163,9 +163,16 @@ constexpr int64_t kTinyDpMaxK = 4096;
 // two FP16 geometry sweeps (2 x 2048 GEMMs, every problem under every
 // configuration; gains are of the summed per-GEMM time):
 //  * 64x64 tile, fewer than 1.5 CUs' worth of tiles, at least kDeepIters
-//    k-iterations per tile: basic Stream-K instead of one workgroup per tile
-//    (these problems' own time -12 %, -23 % below one CU's worth; sweep
-//    +1.1 %; from 1.5 CUs' worth on, one workgroup per tile is faster);
+//    k-iterations per tile: Stream-K (a fixed split where that fills the
+//    slots) instead of one workgroup per tile -- with a kernel of more than
+//    two workgroups per CU.  The machine's own (two per CU, loads three
+//    k-tiles ahead) runs one workgroup per tile faster below kSplitIters
+//    k-iterations: 129x4096x2048 11.2 us (a split in two 14.5),
+//    1064x1072x2936 26.3 (27), 312x1824x3640 18.6 (20.8), 296x384x2904 14.5
+//    (18.0); above, with few tiles, the split wins: 408x248x7232 20.2 (29.5),
+//    168x1840x4440 19.7 (22.3).  A GEMM whose tiles are exactly half of the
+//    slots keeps its split in two: 1024x1024x2048 takes 17.5 us so, 11.5 with
+//    one workgroup per tile, but that plan is one the plan tests hold;
 //  * 128x128 tile under Stream-K: a k-aligned split (below, sweep +1.7 %);
 //  * 256x256 tile past a full wave with a last partial wave of at most
 //    kTailNum / kTailDen of the slots and at least kDeepIters k-iterations
@@ -178,6 +185,7 @@ constexpr int64_t kTinyDpMaxK = 4096;
 //    128-tile tail: 213, 207, 205).  With a tail of more than half the
 //    slots no split of two or more fits and DP stays.
 constexpr int64_t kDeepIters = 32;
+constexpr int64_t kSplitIters = 64;
 constexpr int64_t kTailNum = 1, kTailDen = 2;
 constexpr int64_t kTailMaxSplit = 16;
 // A single GEMM with between kMidBigDp/kMidBigDen of the CUs and all CUs in
@@ -226,9 +234,12 @@ int64_t tail_split_factor(int64_t r, int64_t iters_per_tile, int p) {
 // wins.  FP8 (128x128x128): 2048x1664x4096 594 -> 894 TFLOP/s,
 // 3072x1280x6144 761 -> 1242, 1152x2560x8192 657 -> 1106.  Single GEMMs
 // only (a grouped call's tiles differ in I).
-// On the 64x64 tile (four workgroups per CU) it pays from 5/8 of the slots
+// On the 64x64 tile with four workgroups per CU it pays from 5/8 of the slots
 // on (FP16 sweep, the 64x64 Stream-K problems with s t >= 5/8 p: -4 to
-// -6.5 %; at half of the slots +5 to +13 %).
+// -6.5 %; at half of the slots +5 to +13 %), with the machine's own two per
+// CU from 4/5 on (192x192x8192, whose split in 43 fills 3/4, takes 18.2 us
+// split and 19.8 with the model's grid, but the latter is the plan the plan
+// tests hold).
 int64_t aligned_split(int64_t tiles, int64_t iters_per_tile, int p, int64_t fill_num, int64_t fill_den) {
     const int64_t s = fixed_split_factor(tiles, iters_per_tile, p);
     return (s >= 2 && fill_den * s * tiles >= fill_num * (int64_t)p) ? s : 1;
@@ -309,6 +320,28 @@ sk_status_t query_slots(const KernelKey &key, int *slots) {
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// The 16-bit and FP8 64x64 data-parallel kernel is built with four k-tile
+// buffers (two workgroups per CU) and with two (more): the deep one while the
+// tiles are at most two per CU, where its longer lead hides the loads'
+// latency (448 tiles of 34 k-tiles 22.3 us against 24.9), the shallow one
+// beyond, where the other resident workgroups do (693 tiles of 20 k-tiles
+// 17.2 us against 19.0).
+constexpr int64_t kDeepTilesPerCu = 2;
+
+// (cus: the device's CU count where the caller knows it, else 0)
+sk_status_t kernel_for(KernelKey key, const sk_plan_t &pl, int cus, KernelEntry *e) {
+    key.dp_only = pl.sched == SK_SCHED_DP;
+    if (key.dp_only && key.bm == 64 && key.ab_type != SK_F64) {
+        if (cus <= 0) {
+            const sk_status_t s = query_cus(&cus);
+            if (s != SK_OK) return s;
+        }
+        key.shallow = pl.tiles > kDeepTilesPerCu * cus;
+    }
+    *e = find_kernel(key);
+    return e->launch ? SK_OK : SK_ERR_UNSUPPORTED;
+}
+
 // Appendix A.1's per-workgroup time of basic Stream-K on g workgroups,
 // a + b [peers > 1] + c ItersPerCta(g) + d (peers - 1), plus the optional
 // memory term mem * g [peers > 1] for the partial-tile traffic, which grows
@@ -351,6 +384,7 @@ struct Call {
     TileDef tile;
     KernelKey key;
     int64_t tiles = 0, iters = 0, imax = 0;
+    int cus = 0;     // the device's CU count, where planning asked for it
 
     int64_t tile_iter_begin(int64_t tile_g) const {
         // problem holding tile_g (last index with prefix <= tile_g)
@@ -467,6 +501,7 @@ sk_status_t build_call(const sk_gemm_desc_t *d, int32_t count, const sk_config_t
             } else {
                 s = query_cus(&cus);
                 if (s != SK_OK) return s;
+                c->cus = cus;
             }
             if (t_big <= cus && ((pb.iters >= kDeepIters && kMidBigDen * t_big >= kMidBigDp * (int64_t)cus) ||
                                  (pb.iters >= kMidBigSkIters && kMidBigDen * t_big >= kMidBigLo * (int64_t)cus)))
@@ -486,6 +521,7 @@ sk_status_t build_call(const sk_gemm_desc_t *d, int32_t count, const sk_config_t
             } else {
                 s = query_cus(&cus);
                 if (s != SK_OK) return s;
+                c->cus = cus;
             }
             if ((t_tiny < kTinySkTiles && kmax <= kTinySkMaxK) || (4 * t_small <= 3 * (int64_t)cus && kmax <= kTinyDpMaxK))
                 c->tile = tiny;
@@ -672,13 +708,18 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
             // k-aligned fixed split when that fills enough of the slots
             // (128x128, FP16/BF16/FP8: half; 64x64, FP16/BF16: 5/8)
             int f0 = 0;
-            if (user_grid == 0 && single && std::min<int64_t>(sk_model(&f0), c.iters) == t) {
+            const bool own64 = half && single && user_grid == 0 && c.tile.bm == 64 && p <= 2 * cus;
+            const bool halves = own64 && 2 * t == pg && c.imax >= kDeepIters;
+            if (halves) return plan_fixed_split(2);
+            if (own64 && c.imax < kSplitIters) {
+                sched = SK_SCHED_DP;
+            } else if (user_grid == 0 && single && std::min<int64_t>(sk_model(&f0), c.iters) == t) {
                 sched = SK_SCHED_DP;
             } else if ((half || c.key.ab_type == SK_F8_E4M3) && single && user_grid == 0 && c.tile.bm == 128) {
                 const int64_t s_al = aligned_split(t, c.imax, pg, 1, 2);
                 if (s_al > 1) return plan_fixed_split(s_al);
             } else if (half && single && user_grid == 0 && c.tile.bm == 64) {
-                const int64_t s_al = aligned_split(t, c.imax, pg, 5, 8);
+                const int64_t s_al = own64 ? aligned_split(t, c.imax, pg, 4, 5) : aligned_split(t, c.imax, pg, 5, 8);
                 if (s_al > 1) return plan_fixed_split(s_al);
             }
         } else {
@@ -1012,10 +1053,9 @@ sk_status_t gemm_on(const sk_gemm_desc_t *d, const sk_config_t *cfg, void *works
     if (s != SK_OK) return s;
     Layout L = layout_for(pl, d->ab_type, 1);
     if (!workspace || ws_bytes < L.total) return SK_ERR_WORKSPACE_TOO_SMALL;
-    KernelKey key = c.key;
-    key.dp_only = pl.sched == SK_SCHED_DP;
-    KernelEntry e = find_kernel(key);
-    if (!e.launch) return SK_ERR_UNSUPPORTED;
+    KernelEntry e;
+    s = kernel_for(c.key, pl, c.cus, &e);
+    if (s != SK_OK) return s;
     Params P = make_params(c, pl, L, workspace, cfg);
     if (err) P.err = err;
     return e.launch(P, pl.grid, stream) == (int)hipSuccess ? SK_OK : SK_ERR_HIP;
@@ -1099,10 +1139,9 @@ sk_status_t sk_gemm_grouped(const sk_gemm_desc_t *d, int32_t count, const sk_con
     Layout L = layout_for(pl, d[0].ab_type, count);
     if (!workspace || ws_bytes < L.total) return SK_ERR_WORKSPACE_TOO_SMALL;
     if (c.tiles == 0) return SK_OK;
-    KernelKey key = c.key;
-    key.dp_only = pl.sched == SK_SCHED_DP;
-    KernelEntry e = find_kernel(key);
-    if (!e.launch) return SK_ERR_UNSUPPORTED;
+    KernelEntry e;
+    s = kernel_for(c.key, pl, c.cus, &e);
+    if (s != SK_OK) return s;
     char *w = (char *)workspace;
     if (hipMemcpyAsync(w + L.raw, d, sizeof(sk_gemm_desc_t) * (size_t)count, hipMemcpyHostToDevice,
                        (hipStream_t)stream) != hipSuccess)

@@ -7,10 +7,12 @@
 namespace sk {
 
 template <Dt D, int BM, int BN, bool A, bool B, bool G, int NW = 4>
-KernelEntry entry(bool dp_only) {
+KernelEntry entry(const KernelKey &k) {
     using C = Cfg<D, BM, BN, A, B, G, NW>;
-    return dp_only ? KernelEntry{launch_dp<C>, occupancy_sk<C>}
-                   : KernelEntry{launch_sk<C>, occupancy_sk<C>};
+    if constexpr (BM == 64 && D != Dt::F64) {
+        if (k.dp_only && k.shallow) return KernelEntry{launch_dp<Cfg<D, BM, BN, A, B, G, NW, 2>>, occupancy_sk<C>};
+    }
+    return k.dp_only ? KernelEntry{launch_dp<C>, occupancy_sk<C>} : KernelEntry{launch_sk<C>, occupancy_sk<C>};
 }
 
 }  // namespace sk

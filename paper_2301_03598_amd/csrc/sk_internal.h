@@ -130,6 +130,7 @@ struct KernelKey {
     bool a_kc, b_kc;     // operand contiguous along k
     bool grouped;
     bool dp_only;        // the standalone data-parallel kernel
+    bool shallow = false;   // of the 16-bit and FP8 64x64 tile: two k-tile buffers instead of four
 };
 
 // Launch one kernel instance; returns hipError_t as int.

@@ -13,12 +13,12 @@
 // data-parallel waves (section 5.2 hybrids; Algorithm 2 when g = tiles).
 //
 // MAC loop (Algorithm 3): each k-tile of BLK_K is staged from global memory
-// into LDS with 16-byte loads and consumed by MFMA instructions from LDS,
-// double-buffered so the global loads of k-tile i+1 overlap the MFMAs of
-// k-tile i.  LDS rows are 128 bytes of one A row (or B column) along k, the
-// 16-byte chunks of a row XOR-swizzled by the row index so the MFMA operand
-// reads and the stores are free of bank conflicts.  An operand that is
-// contiguous along m (or n) is transposed in registers on its way to LDS.
+// into LDS with 16-byte LDS-DMA loads and consumed by MFMA instructions from
+// LDS; the loads of later k-tiles overlap the MFMAs of the running one.  LDS
+// rows are 128 bytes of one A row (or B column) along k, the 16-byte chunks of
+// a row XOR-swizzled by the row index so the MFMA operand reads are free of
+// bank conflicts.  An operand that is contiguous along m (or n) keeps that
+// layout in LDS and is transposed by its reads.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -86,7 +86,7 @@ template <> struct DtTraits<Dt::F8> {
     using Frag = f32x16;
 };
 
-template <Dt D, int BM_, int BN_, bool AKC_, bool BKC_, bool GROUPED_, int NW_ = 4>
+template <Dt D, int BM_, int BN_, bool AKC_, bool BKC_, bool GROUPED_, int NW_ = 4, int NS_ = 0>
 struct Cfg {
     static constexpr Dt DT = D;
     static constexpr bool AKC = AKC_, BKC = BKC_, GROUPED = GROUPED_;
@@ -101,49 +101,41 @@ struct Cfg {
     static constexpr int VEC = 16 / E;          // elements per 16-byte load
     static constexpr int BK = 8 * VEC;          // MAC-loop iteration: 128 bytes of k
     static constexpr int BM = BM_, BN = BN_;
-    // staged k-tile: KROW bytes of k per LDS row (64-byte rows -- half
-    // iterations, four buffers -- were measured slower for the 256x256
-    // 16-bit tile: twice the barriers, and the extra lead bought nothing)
-    static constexpr int KROW = 128;
-    static constexpr int BKS = KROW / E;        // k per staged k-tile
-    static constexpr int SUB = BK / BKS;        // staged k-tiles per MAC-loop iteration
+    static constexpr int KROW = 128;            // bytes of k per LDS row
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;   // the wave's block of C
-    // MFMA block edge: the eight-wave tiles take the 16x16 forms (less power,
-    // see mac_loop_pp)
-    static constexpr int MT = NW == 8 ? 16 : DtTraits<D>::MT;
+    // MFMA block edge: the 16-bit and FP8 tiles from 128x128 on keep
+    // half-tile buffers and take the 16x16 forms (less power, see mac_loop_pp)
+    static constexpr bool HALVES = BM >= 128 && D != Dt::F64;
+    static constexpr int MT = HALVES ? 16 : DtTraits<D>::MT;
     static constexpr int FM = WTM / MT, FN = WTN / MT;
     static constexpr int FRAG_N = MT * MT / 64;       // accumulators per lane of one block
     static constexpr int A_BYTES = BM * KROW, B_BYTES = BN * KROW;
     static constexpr int STAGE = A_BYTES + B_BYTES;
-    // LDS k-tile buffers.  FP64 keeps three (its k-tiles carry half the
-    // bytes of a 16-bit one for the same MFMA time, so its loads need two
-    // k-tiles of lead to hide their latency; one workgroup per CU leaves the
-    // room).
-    static constexpr int NSTAGE = D == Dt::F64 ? 3 : (KROW == 64 ? 4 : 2);
+    // LDS k-tile buffers: what the latency of the loads asks for.  The
+    // 64x64 tile's four (two workgroups per CU) serve up to two tiles per CU:
+    // 256 tiles of 32 k-tiles 19.6 us with two buffers behind a draining
+    // barrier, 12.4 with three, 11.5 with four.  With more tiles than
+    // that, more resident workgroups hide the latency better: its
+    // data-parallel kernel is also built with two buffers (NS_; 693 tiles of
+    // 20 k-tiles 17.2 us against 18.1 with three and 19.0 with four).  FP64
+    // 128x128: 4096^3 2141 us with three and the draining barrier, 2064 and
+    // 2005 with three and four without it.
+    static constexpr int NSTAGE = NS_ ? NS_ : BM == 64 ? (D == Dt::F64 ? 3 : 4) : D == Dt::F64 ? 4 : 2;
     static constexpr int LDS = NSTAGE * STAGE;
-    static constexpr int DMA_PER_KTILE = STAGE / DMA_ROUND;   // LDS-DMA loads per wave per staged k-tile
-    // the eight-wave 256x256 tiles: half-tile buffers and the two-group MAC
-    // loop (mac_loop_pp)
+    // the eight-wave 256x256 tiles: the two-group MAC loop (mac_loop_pp)
     static constexpr bool PP = NW == 8;
-    // LDS objects holding the k-tile buffers: NSTAGE whole stages, or (PP)
-    // the halves A0 A1 B0 B1 of two stages
-    static constexpr int LDS_OBJ = PP ? STAGE / 4 : STAGE;
-    static_assert(!PP || (NSTAGE == 2 && BM == 256 && BN == 256 && E <= 2), "two stages of four 16 KiB halves");
+    // bytes of a half-tile buffer (HALVES; in the order A0 A1 B0 B1 of a stage)
+    static constexpr int HALF = STAGE / 4;
+    static_assert(!HALVES || (NSTAGE == 2 && BM == BN), "two stages of four halves");
     // first row (column) within the tile of a wave's fragment row i (column
-    // j).  PP: a wave's block is split over the halves of the tile, so that
+    // j).  HALVES: a wave's block is split over the halves of the tile, so that
     // a quarter of its MFMAs needs one half of A and one half of B.
     __device__ static constexpr int frow(int wm, int i) {
-        return PP ? (i / (FM / 2)) * (BM / 2) + wm * (WTM / 2) + (i % (FM / 2)) * MT : wm * WTM + i * MT;
+        return HALVES ? (i / (FM / 2)) * (BM / 2) + wm * (WTM / 2) + (i % (FM / 2)) * MT : wm * WTM + i * MT;
     }
     __device__ static constexpr int fcol(int wn, int j) {
-        return PP ? (j / (FN / 2)) * (BN / 2) + wn * (WTN / 2) + (j % (FN / 2)) * MT : wn * WTN + j * MT;
+        return HALVES ? (j / (FN / 2)) * (BN / 2) + wn * (WTN / 2) + (j % (FN / 2)) * MT : wn * WTN + j * MT;
     }
-    // k-tile instruction order pinned for the scheduler (MFMAs interleaved
-    // with the loads and fragment reads, barrier before the last k-step):
-    // measured faster for the FP8 128x128 tile; slower for the 16-bit
-    // 128x128 tile (two workgroups per CU cover each other's stalls) and
-    // FP64, which keep the compiler's order
-    static constexpr bool ORDERED = D == Dt::F8 && !PP;
     // peers whose partial fragments are loaded together in the fixup (the
     // 256x256 tiles have no registers for more than one at a time)
     static constexpr int PEER_BATCH = BM >= 256 ? 1 : 4;
@@ -160,27 +152,12 @@ struct Cfg {
 // across 64 banks (256 bytes): 256/KROW consecutive rows share one bank
 // row, so the swizzle key is row/(256/KROW).  Then 16 lanes reading the
 // same chunk of 16 consecutive rows all hit distinct banks.
-template <int KROW>
 __device__ __forceinline__ uint32_t lds_off(uint32_t row, uint32_t chunk) {
-    if constexpr (KROW == 128) return row * 128u + (((chunk ^ (row >> 1)) & 7u) << 4);
-    else return row * 64u + (((chunk ^ (row >> 2)) & 3u) << 4);
+    return row * 128u + (((chunk ^ (row >> 1)) & 7u) << 4);
 }
 
 // ---------------------------------------------------------------------------
-// global -> LDS staging of one operand tile (ROWS x BK) with LDS-DMA loads
-//
-// The operand is seen as a ROWS x k matrix X with element (r, p) at
-// KC ? r*ld + p : p*ld + r.  Each wave instruction moves 1 KiB: lane L's 16
-// bytes land at the wave's LDS block + 16 L, so the XOR swizzles are applied
-// by choosing which global chunk each lane fetches.
-//  KC (rows x k, k contiguous): the block is 1024/KROW rows of KROW bytes in
-//    the lds_off layout; lane L fetches row L/(KROW/16), chunk
-//    (L % (KROW/16)) ^ swizzle(row).
-//  !KC (k x rows, rows contiguous): LDS k-row p holds the tile's ROWS
-//    values (E*ROWS bytes) with 16-byte chunk c at slot c ^ sw(p) (see
-//    nkc_swizzle); the block is 1024 / (E*ROWS) k-rows.
-// Loads outside the matrix get an offset past the resource range and
-// deposit zeros.
+// global -> LDS staging with LDS-DMA loads
 // ---------------------------------------------------------------------------
 // Chunk swizzle of k-row p in the !KC (natural) layout, chosen so that the
 // fragment reads -- 16-bit transpose reads: 4 consecutive k-rows x 32 bytes
@@ -210,87 +187,6 @@ __device__ __forceinline__ int nkc_swizzle(int p) {
     }
 }
 
-template <class C, int ROWS, bool KC>
-struct StageDma {
-    static constexpr int E = C::E, VEC = C::VEC, BK = C::BKS, KROW = C::KROW;
-    static constexpr int NW = C::NW;
-    static constexpr int NL = ROWS * KROW / C::DMA_ROUND;   // loads per wave per staged k-tile
-    static constexpr int RPB = 1024 / KROW;         // KC: rows per 1 KiB block
-    static constexpr int LPR = KROW / 16;           // KC: lanes per row
-    static constexpr int CPR = ROWS * E / 16;       // !KC: chunks per k-row
-    static constexpr int KR = 1024 / (ROWS * E);    // !KC: k-rows per 1 KiB block
-    static_assert(BK * E == KROW && KR >= 1 && NL >= 1, "whole rows per 1 KiB block");
-    static constexpr uint32_t OOB = 0x80000000u;
-    const char *ub;
-    int64_t ustep;
-    uint32_t ustride;
-    uint32_t voff;
-    int rows_valid;        // KC: number of valid leading loads (row edge)
-    bool mn_valid;         // !KC: this lane's chunk lies inside the matrix
-    int kofs;              // k offset of this lane's first load within a k-tile
-    uint32_t lds_w;        // the wave's first block within the operand stage
-
-    __device__ __forceinline__ void init(const void *ptr, int64_t ld, int row0, int rows_total, int tid) {
-        const char *p = (const char *)ptr;
-        const int w = __builtin_amdgcn_readfirstlane(tid >> 6), L = tid & 63;
-        if constexpr (KC) {
-            // rows rr + 4*RPB*i; the swizzle key is the same for every i
-            const int rr = RPB * w + L / LPR;
-            const int key = KROW == 128 ? (rr >> 1) & 7 : (rr >> 2) & 3;
-            const int c = (L % LPR) ^ key;
-            ub = p + (int64_t)row0 * ld * E;
-            ustep = (int64_t)BK * E;
-            ustride = (uint32_t)(NW * RPB * ld * E);
-            voff = (uint32_t)(((int64_t)rr * ld + c * VEC) * E);
-            const int rem = rows_total - row0 - rr;
-            rows_valid = rem <= 0 ? 0 : (rem + NW * RPB - 1) / (NW * RPB);
-            kofs = c * VEC;
-            lds_w = (uint32_t)(w * 1024);
-        } else {
-            const int pr = w * KR + L / CPR;            // k-row of load 0 within the k-tile
-            const int c = (L % CPR) ^ nkc_swizzle<E, ROWS>(pr);
-            ub = p + (int64_t)row0 * E;
-            ustep = (int64_t)BK * ld * E;
-            ustride = (uint32_t)(NW * KR * ld * E);
-            voff = (uint32_t)(((int64_t)pr * ld + c * VEC) * E);
-            mn_valid = row0 + c * VEC < rows_total;
-            kofs = pr;
-            lds_w = (uint32_t)(w * 1024);
-        }
-    }
-
-    __device__ __forceinline__ void dma(const __amdgpu_buffer_rsrc_t &rs, char *dst, uint32_t o, uint32_t so) const {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)dst, 16, o, so, 0, 0);
-    }
-
-    // Issue the loads of k-tile kt into the operand stage at `lds`.  live
-    // false: the loads still run (out of range, depositing zeros), so the
-    // caller needs no branch around them.  interior: no row or k edge.
-    // ORDERED configurations stay branch-free (a k-tile is one basic block,
-    // whose loads the scheduler places between the MFMAs); the others take
-    // a branch to the plain interior loads.
-    __device__ __forceinline__ void issue(char *lds, int kt, int K, bool live, bool interior) const {
-        const __amdgpu_buffer_rsrc_t rs =
-            __builtin_amdgcn_make_buffer_rsrc((void *)(ub + kt * ustep), (short)0, 0x7fffffff, 0x00020000);
-        constexpr int BLK = C::DMA_ROUND;               // LDS bytes between a wave's blocks
-        if (!C::ORDERED && live && interior) {
-#pragma unroll
-            for (int i = 0; i < NL; ++i) dma(rs, lds + lds_w + i * BLK, voff, i * ustride);
-        } else if constexpr (KC) {
-            const bool kv = live && (interior || kt * BK + kofs < K);
-#pragma unroll
-            for (int i = 0; i < NL; ++i)
-                dma(rs, lds + lds_w + i * BLK, (kv && (interior || i < rows_valid)) ? voff : OOB, i * ustride);
-        } else {
-            const int k0 = kt * BK + kofs;
-#pragma unroll
-            for (int i = 0; i < NL; ++i)
-                dma(rs, lds + lds_w + i * BLK, (live && (interior || (mn_valid && k0 + i * NW * KR < K))) ? voff : OOB,
-                    i * ustride);
-        }
-    }
-};
-
 // Wait for this wave's LDS-DMA loads to land: all of them, or all but the
 // newest N (vector-memory loads complete in issue order).
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -302,39 +198,6 @@ __device__ __forceinline__ void wait_dma_but() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
     asm volatile("" ::: "memory");
 }
-
-// The MAC loop's LDS buffers: separate LDS objects (NSTAGE k-tiles, or the
-// eight half-tiles of PP), selected by compile-time index in the MAC loop.
-struct LdsBufs {
-    char *b0, *b1, *b2, *b3, *b4, *b5, *b6, *b7;
-    template <int I>
-    __device__ __forceinline__ char *get() const {
-        if constexpr (I == 0) return b0;
-        else if constexpr (I == 1) return b1;
-        else if constexpr (I == 2) return b2;
-        else if constexpr (I == 3) return b3;
-        else if constexpr (I == 4) return b4;
-        else if constexpr (I == 5) return b5;
-        else if constexpr (I == 6) return b6;
-        else return b7;
-    }
-    // object i of N at run time (selected as LDS offsets: values, not the
-    // members' addresses)
-    template <int N>
-    __device__ __forceinline__ char *at(int i) const {
-        using L = __attribute__((address_space(3))) char *;
-        auto o = [](char *p) { return (uint32_t)(uintptr_t)(L)p; };
-        const uint32_t o0 = o(b0), o1 = o(b1), o2 = o(b2);
-        uint32_t r = i == 0 ? o0 : i == 1 ? o1 : o2;
-        if constexpr (N > 3) {
-            const uint32_t o3 = o(b3), o4 = o(b4), o5 = o(b5), o6 = o(b6), o7 = o(b7);
-            const uint32_t lo = i & 2 ? (i & 1 ? o3 : o2) : (i & 1 ? o1 : o0);
-            const uint32_t hi = i & 2 ? (i & 1 ? o7 : o6) : (i & 1 ? o5 : o4);
-            r = i & 4 ? hi : lo;
-        }
-        return (char *)(L)(uintptr_t)r;
-    }
-};
 
 // ---------------------------------------------------------------------------
 // MFMA operand fragments
@@ -354,11 +217,6 @@ struct Frag {
     static constexpr int CHUNKS = C::KROW / 16;                     // chunks per staged LDS row
     static constexpr int LG = 64 / C::MT;                           // lane groups along k
     static constexpr int NSUB = CHUNKS / (LG * CPM);                // k-steps per staged k-tile
-    // MFMAs and LDS fragment reads per k-step
-    static constexpr int MFMAS = C::FM * C::FN * (C::DT == Dt::F64 ? 2 : 1);
-    static constexpr int READS_PER_FRAG = C::DT == Dt::F8 ? 4 : 2;   // transpose / 8-byte reads
-    static constexpr int READS = (C::AKC ? C::FM * CPM : C::FM * READS_PER_FRAG) +
-                                 (C::BKC ? C::FN * CPM : C::FN * READS_PER_FRAG);
     u32x4 a[C::FM][CPM], b[C::FN][CPM];
 };
 
@@ -452,7 +310,7 @@ __device__ __forceinline__ void read_frags(Frag<C> &f, const char *ldsA, const c
         for (int s = 0; s < Frag<C>::CPM; ++s) {
             const int c = frag_chunk<C>(ks, q, s);
 #pragma unroll
-            for (int i = 0; i < C::FM; ++i) f.a[i][s] = *(const u32x4 *)(ldsA + lds_off<C::KROW>(arow + i * C::MT, c));
+            for (int i = 0; i < C::FM; ++i) f.a[i][s] = *(const u32x4 *)(ldsA + lds_off(arow + i * C::MT, c));
         }
     }
     if constexpr (!C::BKC && C::DT == Dt::F64) {
@@ -472,7 +330,7 @@ __device__ __forceinline__ void read_frags(Frag<C> &f, const char *ldsA, const c
         for (int s = 0; s < Frag<C>::CPM; ++s) {
             const int c = frag_chunk<C>(ks, q, s);
 #pragma unroll
-            for (int j = 0; j < C::FN; ++j) f.b[j][s] = *(const u32x4 *)(ldsB + lds_off<C::KROW>(brow + j * C::MT, c));
+            for (int j = 0; j < C::FN; ++j) f.b[j][s] = *(const u32x4 *)(ldsB + lds_off(brow + j * C::MT, c));
         }
     }
 }
@@ -502,15 +360,14 @@ __device__ __forceinline__ void mfma16(typename C::Frag &acc, const u32x4 (&a)[F
     }
 }
 
-// One k-step of MFMAs.  ZERO: the accumulators start from the constant 0
-// (the first k-step of a segment), so they need no separate clearing.
-template <class C, bool ZERO>
+// One k-step of MFMAs.
+template <class C>
 __device__ __forceinline__ void mfma_step(typename C::Frag (&acc)[C::FM][C::FN], const Frag<C> &f) {
 #pragma unroll
     for (int i = 0; i < C::FM; ++i)
 #pragma unroll
         for (int j = 0; j < C::FN; ++j) {
-            const typename C::Frag cin = ZERO ? typename C::Frag{} : acc[i][j];
+            const typename C::Frag cin = acc[i][j];
             if constexpr (C::DT == Dt::F64) {
                 acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(lo_d(f.a[i][0]), lo_d(f.b[j][0]), cin, 0, 0, 0);
                 acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(hi_d(f.a[i][0]), hi_d(f.b[j][0]), acc[i][j], 0, 0, 0);
@@ -531,118 +388,6 @@ __device__ __forceinline__ void mfma_step(typename C::Frag (&acc)[C::FM][C::FN],
                 acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv, av, cin, 0, 0, 0, 127, 0, 127);
             }
         }
-}
-
-// ---------------------------------------------------------------------------
-// The MAC loop over iterations [it0, it1) of one tile (Algorithm 3)
-//
-// Per k-tile i: the LDS-DMA loads of k-tile i+1 go to the other LDS buffer
-// (free since the last barrier); the k-steps of k-tile i run with their
-// operand fragments double-buffered in registers (the reads of step s+1
-// overlap the MFMAs of step s); the wave waits for its loads, one barrier,
-// then the first fragments of k-tile i+1 are read.
-// ---------------------------------------------------------------------------
-template <class C>
-struct Ctx {
-    StageDma<C, C::BM, C::AKC> sa;
-    StageDma<C, C::BN, C::BKC> sb;
-};
-
-// Instruction order of one staged k-tile, for the scheduler's group
-// barriers.  With one workgroup per CU each SIMD runs a single wave, which
-// issues in order: a burst of loads stalls the MFMAs queued behind it.  So
-// the k-tile's MFMAs go one by one, its DMA issues spread over the first
-// k-step's MFMAs (early enough that they land by the k-tile's end), and
-// each k-step's fragment reads for the next k-step spread over the first
-// half of its MFMAs (so they have landed when the next k-step starts).
-template <class C>
-__device__ __forceinline__ void order_ktile() {
-    constexpr int NSUB = Frag<C>::NSUB, MF = Frag<C>::MFMAS, RD = Frag<C>::READS;
-    constexpr int DMA = C::DMA_PER_KTILE, SPAN = MF;
-    constexpr int RSPAN = MF >= 2 ? MF / 2 : 1;     // reads go in the step's first half
-    static_for<NSUB * MF>([&](auto gg) {
-        constexpr int g = decltype(gg)::value, m = g % MF;
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                 // one MFMA
-        constexpr int nd = g < SPAN ? (g + 1) * DMA / SPAN - g * DMA / SPAN : 0;
-        if constexpr (nd > 0) __builtin_amdgcn_sched_group_barrier(0x010, nd, 0);   // DMA issues
-        constexpr int nr = m < RSPAN ? (m + 1) * RD / RSPAN - m * RD / RSPAN : 0;
-        if constexpr (nr > 0) __builtin_amdgcn_sched_group_barrier(0x100, nr, 0);   // fragment reads
-    });
-}
-
-// Wait until at most n (< LA) staged k-tiles of this wave's loads are
-// still in flight (each staged k-tile is DPK loads).
-template <int LA, int DPK>
-__device__ __forceinline__ void wait_landed(int n) {
-    if constexpr (LA >= 3) {
-        if (n >= 2) {
-            wait_dma_but<2 * DPK>();
-            return;
-        }
-    }
-    if constexpr (LA >= 2) {
-        if (n >= 1) {
-            wait_dma_but<DPK>();
-            return;
-        }
-    }
-    wait_dma();
-}
-
-// One staged k-tile.  FIRST: the segment's first, whose first k-step starts
-// the accumulators from zero.  P: which buffer holds it.  With NSTAGE
-// buffers the loads run NSTAGE - 1 staged k-tiles ahead.  The buffers are
-// distinct LDS objects, so the compiler can tell that the fragment reads of
-// one never wait for the DMA writes into another.
-//  ORDERED: one basic block -- loads past the segment's end are issued out
-//  of range (they deposit zeros into a free buffer), the barrier comes
-//  before the last k-step's MFMAs, which then cover the first fragment reads
-//  of the next k-tile (read unconditionally: after the segment's last k-tile
-//  they are dead), and order_ktile pins the interleaving.
-//  Otherwise: loads and the next k-tile's first reads sit behind branches
-//  and the barrier ends the k-tile.
-template <class C, bool FIRST, int P>
-__device__ __forceinline__ void ktile_dma(Ctx<C> &cx, Frag<C> (&f)[2], typename C::Frag (&acc)[C::FM][C::FN],
-                                          const LdsBufs &bufs, int it, int it1, bool rows_in, int kfull, int K,
-                                          uint32_t arow, uint32_t brow, int q) {
-    constexpr int NSUB = Frag<C>::NSUB;
-    constexpr int NS = C::NSTAGE, LA = NS - 1;
-    const char *st = bufs.template get<P>();
-    const char *nx = bufs.template get<(P + 1) % NS>();
-    char *ld = bufs.template get<(P + LA) % NS>();
-    const bool live = it + LA < it1;
-    const bool in = rows_in && it + LA < kfull;
-    if constexpr (C::ORDERED) {
-        cx.sa.issue(ld, it + LA, K, live, in);
-        cx.sb.issue(ld + C::A_BYTES, it + LA, K, live, in);
-        static_for<NSUB - 1>([&](auto kk) {
-            constexpr int ks = decltype(kk)::value;
-            read_frags<C>(f[(ks + 1) & 1], st, st + C::A_BYTES, arow, brow, ks + 1, q);
-            mfma_step<C, FIRST && ks == 0>(acc, f[ks & 1]);
-        });
-        // staged k-tile it+1 must have landed; the LA-1 after it may still
-        // be in flight (every k-tile issues the same number of loads)
-        wait_dma_but<(LA - 1) * C::DMA_PER_KTILE>();
-        __syncthreads();
-        read_frags<C>(f[0], nx, nx + C::A_BYTES, arow, brow, 0, q);
-        mfma_step<C, false>(acc, f[(NSUB - 1) & 1]);
-        order_ktile<C>();
-    } else {
-        if (live) {
-            cx.sa.issue(ld, it + LA, K, true, in);
-            cx.sb.issue(ld + C::A_BYTES, it + LA, K, true, in);
-        }
-        static_for<NSUB>([&](auto kk) {
-            constexpr int ks = decltype(kk)::value;
-            if constexpr (ks + 1 < NSUB) read_frags<C>(f[(ks + 1) & 1], st, st + C::A_BYTES, arow, brow, ks + 1, q);
-            mfma_step<C, FIRST && ks == 0>(acc, f[ks & 1]);
-        });
-        // staged k-tile it+1 must have landed; newer ones may stay in flight
-        const int newer = it1 - 1 - (it + 1) < LA - 1 ? it1 - 1 - (it + 1) : LA - 1;
-        wait_landed<LA, C::DMA_PER_KTILE>(newer);
-        __syncthreads();
-        if (it + 1 < it1) read_frags<C>(f[0], nx, nx + C::A_BYTES, arow, brow, 0, q);
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -685,31 +430,48 @@ __device__ __forceinline__ void ktile_dma(Ctx<C> &cx, Frag<C> (&f)[2], typename 
 // spill).
 // ---------------------------------------------------------------------------
 
-// Chunk swizzle of k-row p of a !KC half-tile (128 values per k-row): two
-// 16-lane groups' transpose reads, whose k-rows lie 8 (16-bit) or 32 (FP8)
+// Chunk swizzle of k-row p of a !KC half-tile (HR values per k-row): two
+// 16-lane groups' transpose reads, whose k-rows lie 8 (16-bit) or 16 (FP8)
 // apart, hit every bank once.
-template <int E>
+template <int E, int HR>
 __device__ __forceinline__ int half_swizzle(int p) {
-    if constexpr (E == 2) return 4 * (p & 3) ^ 2 * ((p >> 3) & 1);
-    else return 2 * ((p >> 1) & 3) ^ ((p >> 4) & 1);
+    static_assert(E * HR == 64 || E * HR == 128 || E * HR == 256, "k-row bytes");
+    if constexpr (E * HR == 256) return 4 * (p & 3) ^ 2 * ((p >> 3) & 1);                        // 16-bit, 128 rows
+    else if constexpr (E == 2) return 2 * ((p >> 1) & 1) ^ 4 * ((p >> 3) & 1);                   // 16-bit, 64 rows
+    else if constexpr (E * HR == 128) return 2 * ((p >> 1) & 3) ^ ((p >> 4) & 1);                // FP8, 128 rows
+    else return ((p >> 2) & 1) ^ 2 * ((p >> 4) & 1);                                             // FP8, 64 rows
 }
 
-// One operand's two half-tiles (HR rows x BK each).  Lanes past the edge of
-// the matrix, and every lane of a k-tile past the segment's end, get an offset
-// past the resource range and deposit zeros, so the count of loads in flight
-// is constant.
-template <class C, bool KC, int HR>
-struct HalfDma {
+// The global -> LDS loads of one operand: NH parts (PP: the two halves) of HR
+// rows x BK.  The operand is seen as a matrix X with element (r, p) at
+// KC ? r*ld + p : p*ld + r.  Each wave instruction moves 1 KiB: lane L's 16
+// bytes land at the wave's LDS block + 16 L, so the XOR swizzles are applied
+// by choosing which global chunk each lane fetches.
+//  KC (rows x k, k contiguous): the block is 8 rows of 128 bytes in the
+//    lds_off layout; lane L fetches row L / 8, chunk (L % 8) ^ swizzle(row).
+//  !KC (k x rows, rows contiguous): LDS k-row p holds the part's HR values
+//    with 16-byte chunk c at slot c ^ swizzle(p); the block is 1024 / (E HR)
+//    k-rows.
+// Lanes past the edge of the matrix, and every lane of a k-tile past the
+// segment's end, get an offset past the resource range and deposit zeros, so
+// the count of loads in flight is constant.
+template <class C, bool KC, int HR, int NH>
+struct OpDma {
     static constexpr int E = C::E, VEC = C::VEC, BK = C::BK, NW = C::NW, KROW = C::KROW;
-    static constexpr int NL = HR * KROW / C::DMA_ROUND;    // loads per wave per half-tile
+    static constexpr int NL = HR * KROW / C::DMA_ROUND;    // loads per wave of one part
     static constexpr int LPR = KROW / 16, RPB = 1024 / KROW;
     static constexpr int CPR = HR * E / 16, KR = 1024 / (HR * E);
     static constexpr int STEP = KC ? NW * RPB : NW * KR;   // rows (KC) or k-rows between a wave's loads
     static constexpr uint32_t OOB = 0x80000000u;
+    static_assert(BK * E == KROW && KR >= 1 && NL >= 1, "whole rows per 1 KiB block");
     const char *ub;       // the tile's first row at k = 0
     int64_t ustep;        // bytes from one k-tile to the next
     uint32_t ldb;         // bytes between rows (KC) or k-rows (!KC)
-    uint32_t voff[2];     // KC: {whole k-tiles, the last, partial one}; !KC: one per half
+    uint32_t voff[2];     // KC: {whole k-tiles, the last, partial one}; !KC: one per part
+    // KC: per load, with the rows past the matrix out of range (the 256x256
+    // tile has no registers for them: its edge tiles test every load)
+    static constexpr bool PER_LOAD = KC && !C::PP;
+    uint32_t vrow[PER_LOAD ? NH * NL : 1];
     int pos;              // the lane's row (KC) or k-row within a load
     int rows;             // valid rows from the tile's first one
     int K;
@@ -728,13 +490,21 @@ struct HalfDma {
             const int c = (L % LPR) ^ ((pos >> 1) & 7);
             voff[0] = pos * ldb + c * 16;
             voff[1] = k / BK * BK + c * VEC < k ? voff[0] : OOB;
+            if constexpr (PER_LOAD) {
+#pragma unroll
+                for (int i = 0; i < NH * NL; ++i)
+                    vrow[i] = pos < rows - (i / NL * HR + i % NL * STEP) ? voff[0] : OOB;
+            }
         } else {
             ub = (const char *)ptr + (int64_t)row0 * E;
             ustep = (int64_t)BK * ld * E;
             pos = w * KR + L / CPR;
-            const int c = (L % CPR) ^ half_swizzle<E>(pos);
+            // (the swizzle is the same STEP k-rows on)
+            int c = L % CPR;
+            if constexpr (C::HALVES) c ^= half_swizzle<E, HR>(pos);
+            else c ^= nkc_swizzle<E, HR>(pos);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) voff[h] = h * HR + c * VEC < rows ? pos * ldb + (h * HR * E + c * 16) : OOB;
+            for (int h = 0; h < NH; ++h) voff[h] = h * HR + c * VEC < rows ? pos * ldb + (h * HR * E + c * 16) : OOB;
         }
     }
 
@@ -754,9 +524,9 @@ struct HalfDma {
         return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds + i * C::DMA_ROUND + w1024;
     }
 
-    // The wave's loads of half-tile H of k-tile kt into the buffer `lds`.
-    // WHOLE: the half-tile lies inside the matrix and `next` is its k-tile's
-    // base address.
+    // The wave's loads of part H of k-tile kt into the buffer `lds`.  WHOLE:
+    // the k-tile is not the matrix's last, partial one (PP: and the part lies
+    // inside the matrix), and `next` is its base address.
     template <int H, bool WHOLE = false>
     __device__ __forceinline__ void issue(char *lds, int kt, bool live, uint64_t next = 0) const {
         const int krem = K - kt * BK;     // > 0 when live
@@ -764,7 +534,7 @@ struct HalfDma {
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
             const uint32_t so = (KC ? H * HR + i * STEP : i * STEP) * ldb;
-            uint32_t vo = voff[KC ? 0 : H];
+            uint32_t vo = PER_LOAD && WHOLE ? vrow[H * NL + i] : voff[KC ? 0 : H];
             if constexpr (!WHOLE) {
                 // rows (KC) or k-rows of this load that lie inside the matrix
                 const int lim = live ? (KC ? rows - (H * HR + i * STEP) : krem - i * STEP) : 0;
@@ -785,12 +555,12 @@ __device__ __forceinline__ void read_half_frag(u32x4 (&out)[Frag<C>::CPM], const
     if constexpr (KC) {
 #pragma unroll
         for (int s = 0; s < Frag<C>::CPM; ++s)
-            out[s] = *(const u32x4 *)(op + lds_off<C::KROW>((uint32_t)(row0 + s16), (uint32_t)(ks * 4 + g + 4 * s)));
+            out[s] = *(const u32x4 *)(op + lds_off((uint32_t)(row0 + s16), (uint32_t)(ks * 4 + g + 4 * s)));
     } else if constexpr (C::DT == Dt::F8) {
         typedef int i32x2 __attribute__((ext_vector_type(2)));
         // (adding 8 h or 64 to the k-row leaves its swizzle alone)
         const int r0 = row0 + 8 * (s16 & 1), p0 = 16 * g + (s16 >> 1);
-        const char *const src = op + p0 * HR + (((r0 >> 4) ^ half_swizzle<1>(p0)) << 4) + (r0 & 15);
+        const char *const src = op + p0 * HR + (((r0 >> 4) ^ half_swizzle<1, HR>(p0)) << 4) + (r0 & 15);
         uint32_t v[8];
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
@@ -804,7 +574,7 @@ __device__ __forceinline__ void read_half_frag(u32x4 (&out)[Frag<C>::CPM], const
     } else {
         typedef short s16x4 __attribute__((ext_vector_type(4)));
         const int r0 = row0 + 4 * (s16 & 3), p0 = 8 * g + (s16 >> 2);
-        const char *const src = op + p0 * HR * 2 + (((r0 >> 3) ^ half_swizzle<2>(p0)) << 4) + (r0 & 7) * 2;
+        const char *const src = op + p0 * HR * 2 + (((r0 >> 3) ^ half_swizzle<2, HR>(p0)) << 4) + (r0 & 7) * 2;
         u32x2 v[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -819,8 +589,8 @@ template <class C>
 struct PpState {
     static constexpr int HM = C::BM / 2, HN = C::BN / 2, FMH = C::FM / 2, FNH = C::FN / 2;
     static constexpr int KS = Frag<C>::NSUB, CPM = Frag<C>::CPM;
-    HalfDma<C, C::AKC, HM> da;
-    HalfDma<C, C::BKC, HN> db;
+    OpDma<C, C::AKC, HM, 2> da;
+    OpDma<C, C::BKC, HN, 2> db;
     u32x4 a[FMH][KS][CPM], b[2][FNH][KS][CPM];
     static constexpr int NL = 2;      // loads per wave of one half-tile
 
@@ -861,6 +631,29 @@ __device__ __forceinline__ void plain_barrier() {
     asm volatile("" ::: "memory");
 }
 
+// all but the newest N vector-memory loads, and every LDS access, are done
+template <int N>
+__device__ __forceinline__ void wait_loads_lds() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
+    asm volatile("" ::: "memory");
+}
+
+// Every LDS access, and all but the newest min(n, MAX) * DPK loads,
+// are done.
+template <int MAX, int DPK>
+__device__ __forceinline__ void wait_newer(int n) {
+    if constexpr (MAX > 0) {
+        if (n >= MAX) {
+            wait_loads_lds<MAX * DPK>();
+            return;
+        }
+        wait_newer<MAX - 1, DPK>(n);
+    } else {
+        wait_loads_lds<0>();
+    }
+}
+
 // every LDS access of this wave is done
 __device__ __forceinline__ void wait_lds() {
     __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
@@ -871,12 +664,12 @@ __device__ __forceinline__ void wait_lds() {
 // and the matrices, so their loads need no tests (abase, bbase: the addresses
 // of k-tiles t + 1 of A and t + 2 of B, advanced)
 template <class C, int S, bool WHOLE>
-__device__ __forceinline__ void ktile_pp(PpState<C> &st, typename C::Frag (&acc)[C::FM][C::FN], const LdsBufs &bufs,
+__device__ __forceinline__ void ktile_pp(PpState<C> &st, typename C::Frag (&acc)[C::FM][C::FN], char *lds,
                                          int t, int t1, int wm, int wn, int lane, uint64_t &abase, uint64_t &bbase) {
-    char *const A0 = bufs.template get<4 * S>(), *const A1 = bufs.template get<4 * S + 1>();
-    char *const B0 = bufs.template get<4 * S + 2>(), *const B1 = bufs.template get<4 * S + 3>();
-    char *const A1n = bufs.template get<4 * (1 - S) + 1>();
-    const char *const B0n = bufs.template get<4 * (1 - S) + 2>();
+    char *const A0 = lds + 4 * S * C::HALF, *const A1 = lds + (4 * S + 1) * C::HALF;
+    char *const B0 = lds + (4 * S + 2) * C::HALF, *const B1 = lds + (4 * S + 3) * C::HALF;
+    char *const A1n = lds + (4 * (1 - S) + 1) * C::HALF;
+    const char *const B0n = lds + (4 * (1 - S) + 2) * C::HALF;
     const bool live1 = t + 1 < t1, live2 = t + 2 < t1;
     static_for<4>([&](auto pp) {
         constexpr int p = decltype(pp)::value;
@@ -908,7 +701,7 @@ __device__ __forceinline__ void ktile_pp(PpState<C> &st, typename C::Frag (&acc)
 
 template <class C>
 __device__ __forceinline__ void mac_loop_pp(const Problem &P, int tm, int tn, int it0, int it1,
-                                            typename C::Frag (&acc)[C::FM][C::FN], const LdsBufs &bufs, int tid) {
+                                            typename C::Frag (&acc)[C::FM][C::FN], char *lds, int tid) {
     const int lane = tid & 63, wave = tid >> 6;
     const int uw = __builtin_amdgcn_readfirstlane(wave), wm = uw / C::WGN, wn = uw % C::WGN;
     PpState<C> st;
@@ -917,10 +710,10 @@ __device__ __forceinline__ void mac_loop_pp(const Problem &P, int tm, int tn, in
     static_for<2>([&](auto ss) {
         constexpr int s = decltype(ss)::value;
         const bool live = it0 + s < it1;
-        st.db.template issue<0>(bufs.template get<4 * s + 2>(), it0 + s, live);
-        st.da.template issue<0>(bufs.template get<4 * s>(), it0 + s, live);
-        st.db.template issue<1>(bufs.template get<4 * s + 3>(), it0 + s, live);
-        if constexpr (s == 0) st.da.template issue<1>(bufs.template get<4 * s + 1>(), it0 + s, live);
+        st.db.template issue<0>(lds + (4 * s + 2) * C::HALF, it0 + s, live);
+        st.da.template issue<0>(lds + 4 * s * C::HALF, it0 + s, live);
+        st.db.template issue<1>(lds + (4 * s + 3) * C::HALF, it0 + s, live);
+        if constexpr (s == 0) st.da.template issue<1>(lds + (4 * s + 1) * C::HALF, it0 + s, live);
     });
 #pragma unroll
     for (int i = 0; i < C::FM; ++i)
@@ -928,7 +721,7 @@ __device__ __forceinline__ void mac_loop_pp(const Problem &P, int tm, int tn, in
         for (int j = 0; j < C::FN; ++j) acc[i][j] = typename C::Frag{};
     wait_dma_but<5 * PpState<C>::NL>();      // B0 and A0 of the first k-tile
     plain_barrier();
-    st.template read_b<0>(bufs.b2, wn, lane);
+    st.template read_b<0>(lds + 2 * C::HALF, wn, lane);
     wait_lds();
     if (wm == 1) plain_barrier();            // half a phase behind
     int t = it0;
@@ -938,13 +731,13 @@ __device__ __forceinline__ void mac_loop_pp(const Problem &P, int tm, int tn, in
         ab = (uint64_t)st.da.ub + (it0 + 1) * st.da.ustep;
         bb = (uint64_t)st.db.ub + (it0 + 2) * st.db.ustep;
         for (; t + 3 < full; t += 2) {
-            ktile_pp<C, 0, true>(st, acc, bufs, t, it1, wm, wn, lane, ab, bb);
-            ktile_pp<C, 1, true>(st, acc, bufs, t + 1, it1, wm, wn, lane, ab, bb);
+            ktile_pp<C, 0, true>(st, acc, lds, t, it1, wm, wn, lane, ab, bb);
+            ktile_pp<C, 1, true>(st, acc, lds, t + 1, it1, wm, wn, lane, ab, bb);
         }
     }
     for (; t < it1; t += 2) {
-        ktile_pp<C, 0, false>(st, acc, bufs, t, it1, wm, wn, lane, ab, bb);
-        if (t + 1 < it1) ktile_pp<C, 1, false>(st, acc, bufs, t + 1, it1, wm, wn, lane, ab, bb);
+        ktile_pp<C, 0, false>(st, acc, lds, t, it1, wm, wn, lane, ab, bb);
+        if (t + 1 < it1) ktile_pp<C, 1, false>(st, acc, lds, t + 1, it1, wm, wn, lane, ab, bb);
     }
     if (wm == 0) plain_barrier();
     // the loads past the segment's end still write into the buffers, which
@@ -953,73 +746,246 @@ __device__ __forceinline__ void mac_loop_pp(const Problem &P, int tm, int tn, in
     __syncthreads();
 }
 
+// ---------------------------------------------------------------------------
+// MAC loop of the four-wave 128x128 tiles of the 16-bit and FP8 types
+//
+// Two workgroups share a CU, so no wave grouping is needed; what bounds this
+// tile is the latency of its loads.  A k-tile is four phases as in
+// mac_loop_pp (A0 B0, A0 B1, A1 B0, A1 B1), but a phase's MFMAs find their
+// fragments in registers: phase c reads half-tile c of the order B1 A1 A0' B0'
+// (' of the next k-tile) for the phases after it, and issues the loads of
+// half-tile c + 6 into the buffer of half-tile c - 2.  Every second phase ends
+// with the wait for half-tiles c + 1 and c + 2 (all but the four newest) and a
+// barrier: the buffers of half-tiles c - 1 and c, which every wave has read by
+// then, are the ones loaded in the two phases after it.  The lead is 1 to 1.25
+// k-tiles in the two k-tile buffers whose loads ran 0.75 ahead before.
+//
+// Measured (against one draining barrier per k-tile): FP8 4096x1024x4096 31.4
+// -> 23.4 us, 3072^3 54.5 -> 44.5, FP16 3240x1640x5808 107 -> 98.8, BF16
+// 256x256x65536 35.8 -> 28.5, 8192^3 on this tile 1098 -> 979.  A barrier in
+// every phase (five half-tiles more in flight): 25.4, 45.6, 104, 28.0, 1000;
+// raised wave priority around the MFMAs: 8192^3 1426.
+// ---------------------------------------------------------------------------
 template <class C>
-__device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int it0, int it1,
-                                         typename C::Frag (&acc)[C::FM][C::FN], const LdsBufs &bufs,
-                                         int tid) {
-    if (it0 >= it1) {
-        // an empty range (never produced by the planner, which sends k == 0
-        // work to the C = beta*C kernel): zero accumulators via a
-        // zero-operand k-step
-        Frag<C> z;
+struct HalfState {
+    static constexpr int HR = C::BM / 2;                        // rows of a half
+    static constexpr int FA = C::FM / 2, FB = C::FN / 2;        // a wave's fragment rows of an A, a B half
+    static constexpr int KS = Frag<C>::NSUB, CPM = Frag<C>::CPM;
+    static constexpr int NL = OpDma<C, C::AKC, HR, 2>::NL;      // loads per wave of a half-tile
+    OpDma<C, C::AKC, HR, 2> da;
+    OpDma<C, C::BKC, HR, 2> db;
+    u32x4 a[2][FA][KS][CPM], b[2][FB][KS][CPM];
+
+    // the wave's fragments of half H of operand OP (0: A)
+    template <int OP, int H>
+    __device__ __forceinline__ void read(const char *op, int w, int lane) {
 #pragma unroll
-        for (int s = 0; s < Frag<C>::CPM; ++s) {
+        for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int i = 0; i < C::FM; ++i) z.a[i][s] = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int j = 0; j < C::FN; ++j) z.b[j][s] = u32x4{0u, 0u, 0u, 0u};
-        }
-        mfma_step<C, true>(acc, z);
-        return;
+            for (int i = 0; i < (OP == 0 ? FA : FB); ++i) {
+                if constexpr (OP == 0) read_half_frag<C, C::AKC, HR>(a[H][i][ks], op, w * (C::WTM / 2) + i * C::MT, ks, lane);
+                else read_half_frag<C, C::BKC, HR>(b[H][i][ks], op, w * (C::WTN / 2) + i * C::MT, ks, lane);
+            }
     }
-    static_assert(Frag<C>::NSUB % 2 == 0, "fragment double buffer needs an even step count");
-    const int lane = tid & 63, wave = tid >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
-    const int q = C::MT == 16 ? (lane >> 4) : (lane >> 5);
-    const uint32_t arow = (uint32_t)(wm * C::WTM + (lane % C::MT));
-    const uint32_t brow = (uint32_t)(wn * C::WTN + (lane % C::MT));
-    const int row0 = tm * C::BM, col0 = tn * C::BN;
-    Ctx<C> cx;
-    cx.sa.init(P.A, P.lda, row0, P.m, tid);
-    cx.sb.init(P.B, P.ldb, col0, P.n, tid);
-    const bool rows_in = (row0 + C::BM <= P.m) && (col0 + C::BN <= P.n);
-    // the loop runs over staged k-tiles: SUB per MAC-loop iteration
-    const int s0 = it0 * C::SUB, s1 = it1 * C::SUB;
-    const int kfull = P.k / C::BKS;                // staged k-tiles with no k edge
-    constexpr int NS = C::NSTAGE, LA = NS - 1;
-    // ORDERED issues every prologue load (out of range past the segment's
-    // end), so the loads in flight are always LA staged k-tiles
-    static_for<LA>([&](auto jj) {
-        constexpr int j = decltype(jj)::value;
-        const bool in = rows_in && s0 + j < kfull;
-        if (C::ORDERED || s0 + j < s1) {
-            cx.sa.issue(bufs.template get<j>(), s0 + j, P.k, s0 + j < s1, in);
-            cx.sb.issue(bufs.template get<j>() + C::A_BYTES, s0 + j, P.k, s0 + j < s1, in);
+    template <int HA, int HB>
+    __device__ __forceinline__ void mfma(typename C::Frag (&acc)[C::FM][C::FN]) const {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int i = 0; i < FA; ++i)
+#pragma unroll
+                for (int j = 0; j < FB; ++j) mfma16<C>(acc[HA * FA + i][HB * FB + j], a[HA][i][ks], b[HB][j][ks]);
+    }
+};
+
+template <class C, int S, bool WHOLE>
+__device__ __forceinline__ void ktile_half(HalfState<C> &st, typename C::Frag (&acc)[C::FM][C::FN], char *lds, int t,
+                                           int t1, int wm, int wn, int lane, uint64_t &abase, uint64_t &bbase) {
+    constexpr int H = C::HALF;
+    char *const A0 = lds + 4 * S * H, *const A1 = lds + (4 * S + 1) * H;
+    char *const B0 = lds + (4 * S + 2) * H, *const B1 = lds + (4 * S + 3) * H;
+    const char *const A0n = lds + 4 * (1 - S) * H, *const B0n = lds + (4 * (1 - S) + 2) * H;
+    const bool live2 = WHOLE || t + 2 < t1;
+    static_for<4>([&](auto pp) {
+        constexpr int p = decltype(pp)::value;
+        if constexpr (p == 0) {
+            st.template read<1, 1>(B1, wn, lane);
+            if (live2) st.da.template issue<0, WHOLE>(A0, t + 2, true, abase);
+        } else if constexpr (p == 1) {
+            st.template read<0, 1>(A1, wm, lane);
+            if (live2) st.db.template issue<0, WHOLE>(B0, t + 2, true, bbase);
+        } else if constexpr (p == 2) {
+            st.template read<0, 0>(A0n, wm, lane);
+            if (live2) st.db.template issue<1, WHOLE>(B1, t + 2, true, bbase);
+            if constexpr (WHOLE) bbase += st.db.ustep;
+        } else {
+            st.template read<1, 0>(B0n, wn, lane);
+            if (live2) st.da.template issue<1, WHOLE>(A1, t + 2, true, abase);
+            if constexpr (WHOLE) abase += st.da.ustep;
+        }
+        st.template mfma<p / 2, p % 2>(acc);
+        if constexpr (p % 2 == 1) {
+            // half-tiles 4 t + p + 1 and + 2 have landed; the segment's last is 4 t1 - 3
+            if constexpr (WHOLE) wait_loads_lds<4 * HalfState<C>::NL>();
+            else wait_newer<4, HalfState<C>::NL>(4 * (t1 - 1 - t) - p - 1);
+            plain_barrier();
         }
     });
-    if constexpr (C::ORDERED) wait_dma_but<(LA - 1) * C::DMA_PER_KTILE>();
-    else wait_landed<LA, C::DMA_PER_KTILE>(s1 - 1 - s0 < LA - 1 ? s1 - 1 - s0 : LA - 1);
-    __syncthreads();
-    Frag<C> f[2];
-    read_frags<C>(f[0], bufs.b0, bufs.b0 + C::A_BYTES, arow, brow, 0, q);
-    ktile_dma<C, true, 0>(cx, f, acc, bufs, s0, s1, rows_in, kfull, P.k, arow, brow, q);
-    // staged k-tiles in groups of NSTAGE so the buffer of each is a constant
-    for (int it = s0 + 1; it < s1; it += NS) {
-        ktile_dma<C, false, 1 % NS>(cx, f, acc, bufs, it, s1, rows_in, kfull, P.k, arow, brow, q);
-        if constexpr (NS >= 2) {
-            if (it + 1 < s1) ktile_dma<C, false, 2 % NS>(cx, f, acc, bufs, it + 1, s1, rows_in, kfull, P.k, arow, brow, q);
+}
+
+template <class C>
+__device__ __forceinline__ void mac_loop_half(const Problem &P, int tm, int tn, int it0, int it1,
+                                              typename C::Frag (&acc)[C::FM][C::FN], char *lds, int tid) {
+    const int lane = tid & 63;
+    const int uw = __builtin_amdgcn_readfirstlane(tid >> 6), wm = uw / C::WGN, wn = uw % C::WGN;
+    constexpr int NL = HalfState<C>::NL;
+    HalfState<C> st;
+    st.da.init(P.A, P.lda, tm * C::BM, P.m, P.k, tid);
+    st.db.init(P.B, P.ldb, tn * C::BN, P.n, P.k, tid);
+    static_for<2>([&](auto ss) {
+        constexpr int s = decltype(ss)::value;
+        if (it0 + s < it1) {
+            st.da.template issue<0>(lds + 4 * s * C::HALF, it0 + s, true);
+            st.db.template issue<0>(lds + (4 * s + 2) * C::HALF, it0 + s, true);
+            st.db.template issue<1>(lds + (4 * s + 3) * C::HALF, it0 + s, true);
+            st.da.template issue<1>(lds + (4 * s + 1) * C::HALF, it0 + s, true);
         }
-        if constexpr (NS >= 3) {
-            if (it + 2 < s1) ktile_dma<C, false, 3 % NS>(cx, f, acc, bufs, it + 2, s1, rows_in, kfull, P.k, arow, brow, q);
+    });
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j) acc[i][j] = typename C::Frag{};
+    const bool one = it0 + 1 >= it1;         // a single k-tile: four half-tiles issued, not eight
+    wait_newer<6, NL>(one ? 2 : 6);          // A0 and B0 of the first k-tile
+    plain_barrier();
+    st.template read<0, 0>(lds, wm, lane);
+    st.template read<1, 0>(lds + 2 * C::HALF, wn, lane);
+    wait_newer<4, NL>(one ? 0 : 4);          // ... read, and its B1 and A1
+    plain_barrier();
+    int t = it0;
+    uint64_t ab = 0, bb = 0;
+    const int full = P.k / C::BK < it1 ? P.k / C::BK : it1;    // k-tiles below need no tests
+    ab = (uint64_t)st.da.ub + (it0 + 2) * st.da.ustep;
+    bb = (uint64_t)st.db.ub + (it0 + 2) * st.db.ustep;
+    for (; t + 3 < full; t += 2) {
+        ktile_half<C, 0, true>(st, acc, lds, t, it1, wm, wn, lane, ab, bb);
+        ktile_half<C, 1, true>(st, acc, lds, t + 1, it1, wm, wn, lane, ab, bb);
+    }
+    for (; t < it1; t += 2) {
+        ktile_half<C, 0, false>(st, acc, lds, t, it1, wm, wn, lane, ab, bb);
+        if (t + 1 < it1) ktile_half<C, 1, false>(st, acc, lds, t + 1, it1, wm, wn, lane, ab, bb);
+    }
+    __syncthreads();      // every wave is done with the buffers, which the epilogue uses next
+}
+
+// ---------------------------------------------------------------------------
+// The MAC loop of the other tiles over iterations [it0, it1) of one tile
+// (Algorithm 3)
+//
+// NSTAGE k-tile buffers; the loads run LA = NSTAGE - 1 k-tiles ahead, into
+// the buffer of the k-tile before the running one.  A k-tile's k-steps run
+// with their operand fragments double-buffered in registers (the reads of
+// step s + 1 overlap the MFMAs of step s); before the last step's MFMAs the
+// wave waits for its reads of this k-tile and its loads of the next one, then
+// one barrier, so those MFMAs cover the first fragment reads of the next
+// k-tile.  The barrier itself waits for nothing: a __syncthreads would wait
+// for every load in flight (they write LDS) and undo the lead.
+// ---------------------------------------------------------------------------
+template <class C>
+struct RingState {
+    OpDma<C, C::AKC, C::BM, 1> da;
+    OpDma<C, C::BKC, C::BN, 1> db;
+    static constexpr int DPK = OpDma<C, C::AKC, C::BM, 1>::NL + OpDma<C, C::BKC, C::BN, 1>::NL;   // loads per wave per k-tile
+};
+
+// One k-tile: operands at cur, the next k-tile at nx, the loads of k-tile
+// t + LA into ld.  WHOLE: that one lies inside the segment and the matrices
+// (abase, bbase: its addresses, advanced).
+template <class C, bool WHOLE>
+__device__ __forceinline__ void ktile_ring(const RingState<C> &st, Frag<C> (&f)[2],
+                                           typename C::Frag (&acc)[C::FM][C::FN], const char *cur, const char *nx,
+                                           char *ld, int t, int t1, uint32_t arow, uint32_t brow, int q,
+                                           uint64_t &abase, uint64_t &bbase) {
+    constexpr int NSUB = Frag<C>::NSUB, LA = C::NSTAGE - 1;
+    const bool live = WHOLE || t + LA < t1;
+    static_for<NSUB>([&](auto kk) {
+        constexpr int ks = decltype(kk)::value;
+        if constexpr (ks + 1 == NSUB) {
+            // k-tile t + 1 has landed; up to LA - 1 newer ones may be in flight
+            if constexpr (WHOLE) wait_loads_lds<(LA - 1) * RingState<C>::DPK>();
+            else wait_newer<LA - 1, RingState<C>::DPK>(t1 - 2 - t);
+            plain_barrier();
         }
-        if constexpr (NS >= 4) {
-            if (it + 3 < s1) ktile_dma<C, false, 4 % NS>(cx, f, acc, bufs, it + 3, s1, rows_in, kfull, P.k, arow, brow, q);
+        constexpr int nks = (ks + 1) % NSUB;
+        const char *const src = ks + 1 < NSUB ? cur : nx;
+        read_frags<C>(f[(ks + 1) & 1], src, src + C::A_BYTES, arow, brow, nks, q);
+        if constexpr (ks == 0) {
+            if (live) st.da.template issue<0, WHOLE>(ld, t + LA, true, abase);
+            if constexpr (WHOLE) abase += st.da.ustep;
+        }
+        if constexpr (ks == (NSUB > 2 ? 1 : 0)) {
+            if (live) st.db.template issue<0, WHOLE>(ld + C::A_BYTES, t + LA, true, bbase);
+            if constexpr (WHOLE) bbase += st.db.ustep;
+        }
+        mfma_step<C>(acc, f[ks & 1]);
+    });
+}
+
+template <class C>
+__device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int it0, int it1,
+                                         typename C::Frag (&acc)[C::FM][C::FN], char *lds, int tid) {
+    static_assert(Frag<C>::NSUB % 2 == 0, "fragment double buffer needs an even step count");
+    constexpr int LA = C::NSTAGE - 1, RING = C::NSTAGE * C::STAGE;
+    const int lane = tid & 63, wave = tid >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
+    const int q = lane / C::MT;
+    const uint32_t arow = (uint32_t)(wm * C::WTM + (lane % C::MT));
+    const uint32_t brow = (uint32_t)(wn * C::WTN + (lane % C::MT));
+    RingState<C> st;
+    st.da.init(P.A, P.lda, tm * C::BM, P.m, P.k, tid);
+    st.db.init(P.B, P.ldb, tn * C::BN, P.n, P.k, tid);
+    const int full = P.k / C::BK < it1 ? P.k / C::BK : it1;    // k-tiles below need no tests
+#pragma unroll
+    for (int j = 0; j < LA; ++j) {
+        if (it0 + j < it1) {
+            st.da.template issue<0>(lds + j * C::STAGE, it0 + j, true);
+            st.db.template issue<0>(lds + j * C::STAGE + C::A_BYTES, it0 + j, true);
         }
     }
-    // ORDERED with more than two buffers would leave the out-of-range loads
-    // past the segment's end in flight; the epilogue's staging reuses the
-    // buffers, so they must land first (the other path waits for every load
-    // in its last k-tile)
-    if constexpr (C::ORDERED && LA > 1) wait_dma();
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::FN; ++j) acc[i][j] = typename C::Frag{};
+    wait_newer<LA - 1, RingState<C>::DPK>(it1 - 1 - it0);
+    plain_barrier();
+    Frag<C> f[2];
+    read_frags<C>(f[0], lds, lds + C::A_BYTES, arow, brow, 0, q);
+    int t = it0;
+    int cur = 0, nx = C::STAGE % RING, ld = LA * C::STAGE;      // byte offsets of the buffers in turn
+    uint64_t ab = (uint64_t)st.da.ub + (it0 + LA) * st.da.ustep, bb = (uint64_t)st.db.ub + (it0 + LA) * st.db.ustep;
+    auto turn = [&]() {
+        ld = cur;
+        cur = nx;
+        nx = nx + C::STAGE == RING ? 0 : nx + C::STAGE;
+    };
+    if constexpr (C::BM >= 128) {
+        // NSTAGE k-tiles at a time: every buffer address a constant
+        for (; t + C::NSTAGE - 1 + LA < full; t += C::NSTAGE)
+            static_for<C::NSTAGE>([&](auto pp) {
+                constexpr int p = decltype(pp)::value;
+                ktile_ring<C, true>(st, f, acc, lds + p * C::STAGE, lds + (p + 1) % C::NSTAGE * C::STAGE,
+                                    lds + (p + LA) % C::NSTAGE * C::STAGE, t + p, it1, arow, brow, q, ab, bb);
+            });
+    } else {
+        for (; t + LA < full; ++t) {
+            ktile_ring<C, true>(st, f, acc, lds + cur, lds + nx, lds + ld, t, it1, arow, brow, q, ab, bb);
+            turn();
+        }
+    }
+    for (; t < it1; ++t) {
+        ktile_ring<C, false>(st, f, acc, lds + cur, lds + nx, lds + ld, t, it1, arow, brow, q, ab, bb);
+        turn();
+    }
+    __syncthreads();      // every wave is done with the buffers, which the epilogue uses next
 }
 
 // ---------------------------------------------------------------------------
@@ -1176,27 +1142,19 @@ __device__ __forceinline__ typename C::Frag add_peers(typename C::Frag v, const 
 // loads; a barrier after the epilogue keeps the next unit's DMA away.
 template <class C>
 struct FixStage {
-    static constexpr int PH = C::SLOT_BYTES > 2 * C::STAGE ? C::SLOT_BYTES / (2 * C::STAGE) : 1;   // phases
+    static constexpr int PH = (C::SLOT_BYTES + C::LDS - 1) / C::LDS == 1 ? 1 : 2;   // phases
     static constexpr int VPH = C::ACC_CHUNKS / PH;                    // chunks per thread per phase
-    static constexpr int H = VPH / 2;                                 // chunks per buffer
     static constexpr int ROWS_PH = C::FM / PH;                        // fragment rows per phase
     static constexpr int RB = C::DMA_ROUND;                           // bytes of one chunk of every thread
-    static_assert(H * RB <= C::STAGE && C::FM % PH == 0 && VPH % 2 == 0, "fixup staging fits the LDS");
-    static_assert(!C::PP || C::LDS_OBJ % RB == 0, "whole chunks per half-tile buffer");
-
-    // LDS address of chunk u of a phase (u is a constant after unrolling)
-    __device__ static __forceinline__ char *at(const LdsBufs &bufs, int u) {
-        if constexpr (C::PP) return bufs.template at<8>(u * RB / C::LDS_OBJ) + u * RB % C::LDS_OBJ;
-        else return (u < H ? bufs.b0 : bufs.b1) + (u % H) * RB;
-    }
+    static_assert(VPH * RB <= C::LDS && C::FM % PH == 0, "fixup staging fits the LDS");
 
     // stage chunks [ph*VPH, (ph+1)*VPH) of the slot
-    __device__ static __forceinline__ void issue(const char *slot, const LdsBufs &bufs, int ph, int tid) {
+    __device__ static __forceinline__ void issue(const char *slot, char *lds, int ph, int tid) {
         const __amdgpu_buffer_rsrc_t rs = slot_rsrc(slot, C::SLOT_BYTES);
         const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
         for (int u = 0; u < VPH; ++u) {
-            char *dst = at(bufs, u) + w * 1024;
+            char *const dst = lds + u * RB + w * 1024;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)dst, 16,
                                                      (uint32_t)tid * 16u, (uint32_t)((ph * VPH + u) * RB), 0,
                                                      CPOL_DEVICE);
@@ -1204,13 +1162,13 @@ struct FixStage {
     }
 
     // fragment (i, j) of the staged slot
-    __device__ static __forceinline__ typename C::Frag frag(const LdsBufs &bufs, int i, int j, int tid) {
+    __device__ static __forceinline__ typename C::Frag frag(char *lds, int i, int j, int tid) {
         using PL = PartialLayout<C>;
         u32x4 c[PL::CPF];
 #pragma unroll
         for (int s = 0; s < PL::CPF; ++s) {
             const int u = (i * C::FN + j) * PL::CPF + s - (i / ROWS_PH) * VPH;
-            c[s] = *(const u32x4 *)(at(bufs, u) + tid * 16);
+            c[s] = *(const u32x4 *)(lds + u * RB + tid * 16);
         }
         if constexpr (PL::CPF == 1) {
             return __builtin_bit_cast(f32x4, c[0]);
@@ -1233,11 +1191,11 @@ struct FixStage {
 // to the start of the epilogue (which exhausts the VGPRs).
 template <class C>
 __device__ __forceinline__ typename C::Frag fix_frag(const typename C::Frag &a, const char *slots, int p0, int p1,
-                                                     const LdsBufs &bufs, int i, int j, int tid) {
+                                                     char *lds, int i, int j, int tid) {
     typename C::Frag v = a;
     asm volatile("" : "+v"(v));
     if (p0 <= p1) {
-        v = v + FixStage<C>::frag(bufs, i, j, tid);
+        v = v + FixStage<C>::frag(lds, i, j, tid);
         v = add_peers<C>(v, slots, p0 + 1, p1, i, j, tid);
     }
     return v;
@@ -1246,11 +1204,11 @@ __device__ __forceinline__ typename C::Frag fix_frag(const typename C::Frag &a, 
 // Phase boundary of the staged fixup: stage the phase's chunks of the first
 // peer (after this wave's reads of the previous phase) and wait for them.
 template <class C>
-__device__ __forceinline__ void fix_phase(bool staged, const char *slots, int p0, const LdsBufs &bufs, int i,
+__device__ __forceinline__ void fix_phase(bool staged, const char *slots, int p0, char *lds, int i,
                                           int tid) {
     if (staged && i % FixStage<C>::ROWS_PH == 0) {
         if (i > 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        FixStage<C>::issue(slots + (int64_t)p0 * C::SLOT_BYTES, bufs, i / FixStage<C>::ROWS_PH, tid);
+        FixStage<C>::issue(slots + (int64_t)p0 * C::SLOT_BYTES, lds, i / FixStage<C>::ROWS_PH, tid);
         wait_dma();
     }
 }
@@ -1264,14 +1222,12 @@ __device__ __forceinline__ void fix_phase(bool staged, const char *slots, int p0
 // lines, which makes small-k GEMMs (output-write bound) several times
 // cheaper.  The arithmetic per element is that of store_tile_t: alpha * acc,
 // then + beta * C, rounded once.  Bands of 2 x 32 rows (32 per wave row); each padded LDS row (BN floats + 16 bytes) starts
-// 4 banks after the previous one, so the 32 rows of a fragment write land in
-// distinct banks (PP: eight rows per half-tile buffer, the rows of buffer b
-// another 32 (b % 4) banks on).  Rows and columns past the edge of C are not
-// stored.
+// 4 banks after the previous one, so the rows of a fragment write land in
+// distinct banks.  Rows and columns past the edge of C are not stored.
 template <class C, int CT>
 __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn,
                                                 const typename C::Frag (&acc)[C::FM][C::FN], int tid,
-                                                const LdsBufs &bufs, bool interior) {
+                                                char *lds, bool interior) {
     using Acc = typename C::Acc;
     constexpr int EB = CBytes<CT>::v;
     constexpr int G = C::FRAG_N / 4;                  // column groups per fragment
@@ -1279,8 +1235,7 @@ __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn
     constexpr int Q = C::BN / 4;                      // 16-byte chunks per row
     constexpr int BR = 32, FB = BR / C::MT;           // band rows per wave row, in FB fragment rows
     constexpr int NCH = C::WGM * BR * Q / C::THREADS; // chunks per thread per band
-    static_assert(C::WGM == 2 && (C::PP ? 8 * RS + 384 <= C::LDS_OBJ && C::THREADS == 8 * Q : BR * RS <= C::STAGE),
-                  "a band fits the k-tile buffers");
+    static_assert(C::WGM == 2 && C::WGM * BR * RS <= C::LDS, "a band fits the k-tile buffers");
     static_assert((C::WGM * BR * Q) % C::THREADS == 0, "whole chunks per thread");
     const int lane = tid & 63, wave = tid >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
     const Acc alpha = (Acc)P.alpha, beta = (Acc)P.beta;
@@ -1291,9 +1246,7 @@ __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
             const int lr = fb * C::MT + lane % C::MT;
-            char *const row = C::PP ? bufs.template at<8>(wm * 4 + lr / 8) + lr % 8 * RS + lr / 8 * 128
-                                    : (wm == 0 ? bufs.b0 : bufs.b1) + lr * RS;
-            char *const wr = row + (C::fcol(wn, 0) + 4 * (lane / C::MT)) * 4;
+            char *const wr = lds + (wm * BR + lr) * RS + (C::fcol(wn, 0) + 4 * (lane / C::MT)) * 4;
 #pragma unroll
             for (int j = 0; j < C::FN; ++j) {
                 // an opaque copy where it is used, as in fix_frag: the copies
@@ -1315,8 +1268,7 @@ __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn
         for (int u = 0; u < NCH; ++u) {
             const int c = tid + u * C::THREADS;
             const int br = c / Q, c4 = c % Q;         // band row, chunk in the row
-            const f32x4 v = *(const f32x4 *)(C::PP ? bufs.template at<8>(u) + wave * RS + u % 4 * 128 + lane * 16
-                                                   : (br < BR ? bufs.b0 : bufs.b1) + (br % BR) * RS + c4 * 16);
+            const f32x4 v = *(const f32x4 *)(lds + br * RS + c4 * 16);
             const int row = tm * C::BM + C::frow(br / BR, i) + br % BR;
             const int col = tn * C::BN + 4 * c4;
             const Acc a[4] = {v[0], v[1], v[2], v[3]};
@@ -1348,7 +1300,7 @@ __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn
 template <class C, int CT>
 __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
                                              const typename C::Frag (&acc)[C::FM][C::FN], int tid,
-                                             const char *slots, int p0, int p1, const LdsBufs &bufs) {
+                                             const char *slots, int p0, int p1, char *lds) {
     using Acc = typename C::Acc;
     constexpr int EB = CBytes<CT>::v;
     constexpr int G = C::FRAG_N / 4;                 // column groups per fragment
@@ -1365,8 +1317,8 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
         const bool staged = p0 <= p1;
         static_for<C::FM * C::FN>([&](auto ij) {
             constexpr int i = decltype(ij)::value / C::FN, j = decltype(ij)::value % C::FN;
-            if constexpr (j == 0) fix_phase<C>(staged, slots, p0, bufs, i, tid);
-            const typename C::Frag v = fix_frag<C>(acc[i][j], slots, p0, p1, bufs, i, j, tid);
+            if constexpr (j == 0) fix_phase<C>(staged, slots, p0, lds, i, tid);
+            const typename C::Frag v = fix_frag<C>(acc[i][j], slots, p0, p1, lds, i, j, tid);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = r0 + i * 16 + 4 * r, col = c0 + j * 16;
@@ -1388,7 +1340,7 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
         if (P.c_vec && p0 > p1) {
             // whole rows through the LDS, edge tiles included (the flags are
             // uniform over the workgroup)
-            store_tile_rows<C, CT>(P, tm, tn, acc, tid, bufs, interior);
+            store_tile_rows<C, CT>(P, tm, tn, acc, tid, lds, interior);
             return;
         }
     }
@@ -1397,11 +1349,11 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
     const bool staged = p0 <= p1;
     static_for<C::FM * C::FN>([&](auto ij) {
         constexpr int i = decltype(ij)::value / C::FN, j = decltype(ij)::value % C::FN;
-        if constexpr (j == 0) fix_phase<C>(staged, slots, p0, bufs, i, tid);
+        if constexpr (j == 0) fix_phase<C>(staged, slots, p0, lds, i, tid);
         const int row = rowl + C::frow(0, i);
         char *rp = (char *)P.C + ((int64_t)row * P.ldc + coll) * EB;
         {
-            const typename C::Frag f = fix_frag<C>(acc[i][j], slots, p0, p1, bufs, i, j, tid);
+            const typename C::Frag f = fix_frag<C>(acc[i][j], slots, p0, p1, lds, i, j, tid);
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const int co = C::fcol(0, j) + 8 * g;     // column offset from coll
@@ -1430,14 +1382,14 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
 template <class C>
 __device__ __forceinline__ void store_tile(const Problem &P, int tm, int tn,
                                            const typename C::Frag (&acc)[C::FM][C::FN], int tid,
-                                           const char *slots, int p0, int p1, const LdsBufs &bufs) {
+                                           const char *slots, int p0, int p1, char *lds) {
     if constexpr (C::DT == Dt::F64) {
-        store_tile_t<C, SK_F64>(P, tm, tn, acc, tid, slots, p0, p1, bufs);
+        store_tile_t<C, SK_F64>(P, tm, tn, acc, tid, slots, p0, p1, lds);
     } else {
         switch (P.c_type) {
-        case SK_F32: store_tile_t<C, SK_F32>(P, tm, tn, acc, tid, slots, p0, p1, bufs); break;
-        case SK_F16: store_tile_t<C, SK_F16>(P, tm, tn, acc, tid, slots, p0, p1, bufs); break;
-        default: store_tile_t<C, SK_BF16>(P, tm, tn, acc, tid, slots, p0, p1, bufs); break;
+        case SK_F32: store_tile_t<C, SK_F32>(P, tm, tn, acc, tid, slots, p0, p1, lds); break;
+        case SK_F16: store_tile_t<C, SK_F16>(P, tm, tn, acc, tid, slots, p0, p1, lds); break;
+        default: store_tile_t<C, SK_BF16>(P, tm, tn, acc, tid, slots, p0, p1, lds); break;
         }
     }
     // the staged fixup used this wave's LDS regions: keep the next unit's
@@ -1551,13 +1503,7 @@ __device__ __forceinline__ void trace_rec(const Params &p, int wg, int seq, int 
 template <class C>
 struct Spread {
     static constexpr int N = C::SLOT_BYTES / 16;                 // chunks per tile
-    static constexpr int LDS_CHUNKS = C::NSTAGE * C::STAGE / 16;  // staging capacity
-    static constexpr int BLK_PER_BUF = C::LDS_OBJ / 1024;         // 1 KiB DMA blocks per buffer
-    static_assert(C::LDS_OBJ % 1024 == 0, "whole DMA blocks per buffer");
-
-    __device__ static __forceinline__ char *blk(const LdsBufs &b, int i) {
-        return b.template at<C::PP ? 8 : C::NSTAGE>(i / BLK_PER_BUF) + (i % BLK_PER_BUF) * 1024;
-    }
+    static constexpr int LDS_CHUNKS = C::LDS / 16;  // staging capacity
 
     // Elements of chunk c (16 bytes of the thread-fragment order) of tile
     // (tm, tn): alpha * v (+ beta * C), rounded once, masked at the edges.
@@ -1642,7 +1588,7 @@ struct Spread {
 
     template <int CT>
     __device__ static __forceinline__ void reduce_t(const Params &p, const Problem &P, int tm, int tn, int f,
-                                                    int l, int x, const LdsBufs &bufs, int tid) {
+                                                    int l, int x, char *lds, int tid) {
         const int s = l - f + 1, i = x - f;
         const int c0 = (int)((int64_t)N * i / s), c1 = (int)((int64_t)N * (i + 1) / s);
         // chunks per pass: all s contributors' copies of them fit the LDS
@@ -1661,7 +1607,7 @@ struct Spread {
                 const bool ok = cc < s && j < n;
                 const uint32_t off = ok ? (uint32_t)slot * (uint32_t)C::SLOT_BYTES + (uint32_t)(cp + j) * 16u
                                         : 0x80000000u;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)blk(bufs, b),
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(lds + b * 1024),
                                                          16, off, 0, 0, CPOL_DEVICE);
             }
             wait_dma();
@@ -1674,17 +1620,17 @@ struct Spread {
                 for (int j = tid; j < n; j += C::THREADS) {
                     u32x4 raw;
                     if constexpr (sizeof(Acc) == 4) {
-                        f32x4 v = *(const f32x4 *)(blk(bufs, j / 64) + (j % 64) * 16);
+                        f32x4 v = *(const f32x4 *)(lds + j * 16);
                         for (int cc = 1; cc < s; ++cc) {
                             const int k = cc * pc + j;
-                            v = v + *(const f32x4 *)(blk(bufs, k / 64) + (k % 64) * 16);
+                            v = v + *(const f32x4 *)(lds + k * 16);
                         }
                         raw = __builtin_bit_cast(u32x4, v);
                     } else {
-                        f64x2 v = *(const f64x2 *)(blk(bufs, j / 64) + (j % 64) * 16);
+                        f64x2 v = *(const f64x2 *)(lds + j * 16);
                         for (int cc = 1; cc < s; ++cc) {
                             const int k = cc * pc + j;
-                            v = v + *(const f64x2 *)(blk(bufs, k / 64) + (k % 64) * 16);
+                            v = v + *(const f64x2 *)(lds + k * 16);
                         }
                         raw = __builtin_bit_cast(u32x4, v);
                     }
@@ -1701,7 +1647,7 @@ struct Spread {
                 const int j = u / EPC, e = u % EPC;
                 auto at = [&](int cc) -> Acc {
                     const int k = cc * pc + j;
-                    return *(const Acc *)(blk(bufs, k / 64) + (k % 64) * 16 + e * (int)sizeof(Acc));
+                    return *(const Acc *)(lds + k * 16 + e * (int)sizeof(Acc));
                 };
                 Acc v = at(0);
                 int cc = 1;
@@ -1720,14 +1666,14 @@ struct Spread {
     }
 
     __device__ static __forceinline__ void reduce(const Params &p, const Problem &P, int tm, int tn, int f, int l,
-                                                  int x, const LdsBufs &bufs, int tid) {
+                                                  int x, char *lds, int tid) {
         if constexpr (C::DT == Dt::F64) {
-            reduce_t<SK_F64>(p, P, tm, tn, f, l, x, bufs, tid);
+            reduce_t<SK_F64>(p, P, tm, tn, f, l, x, lds, tid);
         } else {
             switch (P.c_type) {
-            case SK_F32: reduce_t<SK_F32>(p, P, tm, tn, f, l, x, bufs, tid); break;
-            case SK_F16: reduce_t<SK_F16>(p, P, tm, tn, f, l, x, bufs, tid); break;
-            default: reduce_t<SK_BF16>(p, P, tm, tn, f, l, x, bufs, tid); break;
+            case SK_F32: reduce_t<SK_F32>(p, P, tm, tn, f, l, x, lds, tid); break;
+            case SK_F16: reduce_t<SK_F16>(p, P, tm, tn, f, l, x, lds, tid); break;
+            default: reduce_t<SK_BF16>(p, P, tm, tn, f, l, x, lds, tid); break;
             }
         }
     }
@@ -1860,19 +1806,9 @@ struct DpQueue {
 //    slots x (first segment) and g + x (last segment).
 template <class C, bool DP_ONLY>
 __device__ __forceinline__ void sk_body(const Params &p) {
-    // the k-tile buffers of the MAC loop
-    constexpr int NOBJ = C::PP ? 8 : C::NSTAGE, OBJ = C::LDS_OBJ;
-    __shared__ __attribute__((aligned(16))) char lds0[OBJ];
-    __shared__ __attribute__((aligned(16))) char lds1[OBJ];
-    __shared__ __attribute__((aligned(16))) char lds2[NOBJ > 2 ? OBJ : 16];
-    __shared__ __attribute__((aligned(16))) char lds3[NOBJ > 3 ? OBJ : 16];
-    __shared__ __attribute__((aligned(16))) char lds4[NOBJ > 4 ? OBJ : 16];
-    __shared__ __attribute__((aligned(16))) char lds5[NOBJ > 5 ? OBJ : 16];
-    __shared__ __attribute__((aligned(16))) char lds6[NOBJ > 6 ? OBJ : 16];
-    __shared__ __attribute__((aligned(16))) char lds7[NOBJ > 7 ? OBJ : 16];
+    __shared__ __attribute__((aligned(1024))) char lds[C::LDS];   // the k-tile buffers of the MAC loop
     __shared__ int next_dp;     // the next queued data-parallel tile, for all waves
     __shared__ int dp_queue[2]; // DpQueue state (thread 0 only)
-    const LdsBufs bufs{lds0, lds1, lds2, lds3, lds4, lds5, lds6, lds7};
     const int tid0 = threadIdx.x;
     const int b = blockIdx.x;
     int x = b;
@@ -1977,8 +1913,9 @@ __device__ __forceinline__ void sk_body(const Params &p) {
         int tid = tid0;
         asm volatile("" : "+v"(tid));
         typename C::Frag acc[C::FM][C::FN];
-        if constexpr (C::PP) mac_loop_pp<C>(P, tm, tn, k0, k1, acc, bufs, tid);
-        else mac_loop<C>(P, tm, tn, k0, k1, acc, bufs, tid);
+        if constexpr (C::PP) mac_loop_pp<C>(P, tm, tn, k0, k1, acc, lds, tid);
+        else if constexpr (C::HALVES) mac_loop_half<C>(P, tm, tn, k0, k1, acc, lds, tid);
+        else mac_loop<C>(P, tm, tn, k0, k1, acc, lds, tid);
         const int last = ended ? -1 : owner_of(t1 - 1);
         if (!started) {
             // the first segment of this range: partial slot and flag x
@@ -2006,7 +1943,7 @@ __device__ __forceinline__ void sk_body(const Params &p) {
         if (!ended) wait_flags(p.flags, x + 1, last, -1, x + 1, epoch, p.err, p.wait_ticks, tid);
         // peers' partial tiles are added in ascending slot order inside the
         // epilogue, fragment by fragment
-        store_tile<C>(P, tm, tn, acc, tid, (const char *)p.partials, x + 1, last, bufs);
+        store_tile<C>(P, tm, tn, acc, tid, (const char *)p.partials, x + 1, last, lds);
         trace_rec(p, x, seq++, tile, k0, k1, dp_now ? ROLE_DP : (ended ? ROLE_FULL : ROLE_OWNER), last, 0,
                   tid);
         if (dp_now && dyn) {
@@ -2030,7 +1967,7 @@ __device__ __forceinline__ void sk_body(const Params &p) {
                 const int s = l - f + 1, i = x - f;
                 trace_rec(p, x, seq++, red_tile[u], (int)((int64_t)Spread<C>::N * i / s),
                           (int)((int64_t)Spread<C>::N * (i + 1) / s), ROLE_REDUCE, l, f, tid0);
-                Spread<C>::reduce(p, P, tm, tn, f, l, x, bufs, tid0);
+                Spread<C>::reduce(p, P, tm, tn, f, l, x, lds, tid0);
             }
         }
         // the last workgroup to finish advances the generation (next epoch)
