@@ -30,8 +30,6 @@
 
 namespace sk {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -66,24 +64,19 @@ enum class Dt { F64, F16, BF16, F8 };
 template <Dt D> struct DtTraits;
 template <> struct DtTraits<Dt::F64> {
     static constexpr int E = 8;     // bytes per element
-    static constexpr int MT = 16;   // MFMA output block edge
     using Acc = double;
-    using Frag = f64x4;             // one 16x16 output block per lane
 };
 template <> struct DtTraits<Dt::F16> {
-    static constexpr int E = 2, MT = 32;
+    static constexpr int E = 2;
     using Acc = float;
-    using Frag = f32x16;
 };
 template <> struct DtTraits<Dt::BF16> {
-    static constexpr int E = 2, MT = 32;
+    static constexpr int E = 2;
     using Acc = float;
-    using Frag = f32x16;
 };
 template <> struct DtTraits<Dt::F8> {
-    static constexpr int E = 1, MT = 32;
+    static constexpr int E = 1;
     using Acc = float;
-    using Frag = f32x16;
 };
 
 template <Dt D, int BM_, int BN_, bool AKC_, bool BKC_, bool GROUPED_, int NW_ = 4, int NS_ = 0>
@@ -103,12 +96,11 @@ struct Cfg {
     static constexpr int BM = BM_, BN = BN_;
     static constexpr int KROW = 128;            // bytes of k per LDS row
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;   // the wave's block of C
-    // MFMA block edge: the 16-bit and FP8 tiles from 128x128 on keep
-    // half-tile buffers and take the 16x16 forms (less power, see mac_loop_pp)
+    // the 16-bit and FP8 tiles from 128x128 on keep half-tile buffers
     static constexpr bool HALVES = BM >= 128 && D != Dt::F64;
-    static constexpr int MT = HALVES ? 16 : DtTraits<D>::MT;
+    static constexpr int MT = 16;               // MFMA block edge
     static constexpr int FM = WTM / MT, FN = WTN / MT;
-    static constexpr int FRAG_N = MT * MT / 64;       // accumulators per lane of one block
+    static constexpr int FRAG_N = 4;            // accumulators per lane of one block
     static constexpr int A_BYTES = BM * KROW, B_BYTES = BN * KROW;
     static constexpr int STAGE = A_BYTES + B_BYTES;
     // LDS k-tile buffers: what the latency of the loads asks for.  The
@@ -140,7 +132,7 @@ struct Cfg {
     // 256x256 tiles have no registers for more than one at a time)
     static constexpr int PEER_BATCH = BM >= 256 ? 1 : 4;
     using Acc = typename DtTraits<D>::Acc;
-    using Frag = std::conditional_t<MT == 16 && D != Dt::F64, f32x4, typename DtTraits<D>::Frag>;
+    using Frag = std::conditional_t<D == Dt::F64, f64x4, f32x4>;
     static constexpr int ACC_N = FM * FN * FRAG_N;     // accumulators per thread
     static constexpr int ACC_CHUNKS = ACC_N * (int)sizeof(Acc) / 16;
     static constexpr int SLOT_BYTES = BM * BN * (int)sizeof(Acc);
@@ -159,34 +151,6 @@ __device__ __forceinline__ uint32_t lds_off(uint32_t row, uint32_t chunk) {
 // ---------------------------------------------------------------------------
 // global -> LDS staging with LDS-DMA loads
 // ---------------------------------------------------------------------------
-// Chunk swizzle of k-row p in the !KC (natural) layout, chosen so that the
-// fragment reads -- 16-bit transpose reads: 4 consecutive k-rows x 32 bytes
-// per 16 lanes; 8-bit: 8 consecutive k-rows x 16 bytes; FP64: 4 k-rows two
-// apart x 128 bytes -- hit every bank once per 256 bytes.  A k-row of 256
-// bytes fills the 64 banks; one of 128 (64) bytes shares them with 1 (3)
-// neighbours.  The swizzled chunk stays inside its k-row: the value is below
-// the k-row's chunk count (ROWS * E / 16).
-template <int E, int ROWS>
-__device__ __forceinline__ int nkc_swizzle(int p) {
-    constexpr int RB = ROWS * E;     // bytes per k-row
-    static_assert(RB >= 64, "at least four chunks per k-row");
-    if constexpr (E == 8) {
-        static_assert(RB >= 256, "FP64 swizzle needs 16 chunks");
-        return 8 * ((p >> 1) & 1);
-    } else if constexpr (E == 2) {
-        // 256-byte k-rows: the 4 k-rows of a read share the banks;
-        // 128-byte k-rows: k-rows p and p + 2 do
-        if constexpr (RB >= 256) return 4 * (p & 3);
-        else return 2 * ((p >> 1) & 1);
-    } else {
-        // 8 consecutive k-rows per read: 256-byte k-rows all share the banks,
-        // 128-byte ones in fours, 64-byte ones in pairs (p and p + 4)
-        if constexpr (RB >= 256) return 2 * (p & 7);
-        else if constexpr (RB == 128) return 2 * ((p >> 1) & 3);
-        else return 2 * ((p >> 2) & 1);
-    }
-}
-
 // Wait for this wave's LDS-DMA loads to land: all of them, or all but the
 // newest N (vector-memory loads complete in issue order).
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -202,148 +166,37 @@ __device__ __forceinline__ void wait_dma_but() {
 // ---------------------------------------------------------------------------
 // MFMA operand fragments
 //
-// 32x32 MFMAs (f16/bf16/f8): lane l feeds row (l % 32) of the A block (and
-// column (l % 32) of the B block) with a contiguous run of k from lane group
-// q = l / 32: 8 values (one 16-byte chunk) for f16/bf16, 32 values (two
-// chunks) for f8.  A k-tile (8 chunks) is NSUB such k-steps.
-// 16x16x4 f64 MFMA: lane group q = l / 16 supplies one k value per MFMA; one
-// chunk read gives a lane two consecutive k values (2q and 2q+1 of an 8-k
-// half of the row) consumed by two MFMAs.  A and B use the same assignment,
-// so every k of the k-tile meets its partner exactly once.
+// 16x16 blocks: lane l feeds row (l % 16) of the A block (and column (l % 16)
+// of the B block); lane group g = l / 16 holds a part of the k-step's k:
+//  16-bit (16x16x32): 8 values, one 16-byte chunk;
+//  FP8 (16x16x128): 32 values, chunks g and g + 4 of the k-tile's eight;
+//  FP64 (16x16x4): one value per MFMA; a chunk read gives a lane two
+//    consecutive k values (2g and 2g + 1 of an 8-k half of the row) consumed
+//    by two MFMAs.
+// A and B use the same assignment, so every k of the k-tile meets its partner
+// exactly once.  (For the 16-bit and FP8 types the 32x32 forms do the same
+// work with half the accumulator reads per k but draw more power, see
+// mac_loop_pp, and their chains of additions are twice as long.)
 // ---------------------------------------------------------------------------
 template <class C>
 struct Frag {
     static constexpr int CPM = (C::DT == Dt::F8) ? 2 : 1;          // chunks per lane per operand
-    static constexpr int CHUNKS = C::KROW / 16;                     // chunks per staged LDS row
-    static constexpr int LG = 64 / C::MT;                           // lane groups along k
-    static constexpr int NSUB = CHUNKS / (LG * CPM);                // k-steps per staged k-tile
+    static constexpr int NSUB = C::KROW / 64 / CPM;                // k-steps per k-tile
     u32x4 a[C::FM][CPM], b[C::FN][CPM];
 };
-
-template <class C>
-__device__ __forceinline__ int frag_chunk(int ks, int q, int s) {
-    return (ks * Frag<C>::LG + q) * Frag<C>::CPM + s;
-}
-
-// One 16-bit MFMA operand fragment from a !KC operand stage (k-rows of ROWS
-// values, chunk-swizzled): lane l needs rows base + l%32 at k = 8(l/32)..+7 of
-// k-step ks.  ds_read_b64_tr_b16 hands lane l of a 16-lane group element l%4
-// of the 4-value runs read by lanes 4e + (l%16)/4, e = 0..3, so source lane
-// s (s16 = s%16, group g = s/16) reads k-row ks*16 + 8(g/2) + 4h + s16/4 at
-// rows base + 16(g%2) + 4(s16%4); two reads (h = 0, 1) give the 8 k values.
-template <class C, int ROWS>
-__device__ __forceinline__ u32x4 frag_tr(const char *op, uint32_t base, int ks, int lane) {
-    typedef short s16x4 __attribute__((ext_vector_type(4)));
-    constexpr int RB = ROWS * 2;
-    const int g = lane >> 4, s16 = lane & 15;
-    const uint32_t r0 = base + 16 * (g & 1) + 4 * (s16 & 3);
-    const uint32_t p = (uint32_t)(ks * 16 + 8 * (g >> 1) + (s16 >> 2));
-    const uint32_t off = p * RB + (((r0 >> 3) ^ (uint32_t)nkc_swizzle<2, ROWS>((int)p)) << 4) + (r0 & 7) * 2;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(op + off));
-    const s16x4 hi =
-        __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(op + off + 4 * RB));
-    const u32x2 l2 = __builtin_bit_cast(u32x2, lo), h2 = __builtin_bit_cast(u32x2, hi);
-    return u32x4{l2[0], l2[1], h2[0], h2[1]};
-}
-
-// One FP8 MFMA operand fragment (32 k values per lane) from a !KC operand
-// stage: lane l needs rows base + l%32 at k = ks*64 + 32(l/32) + 0..31.
-// ds_read_b64_tr_b8 hands lane l of a 16-lane group byte l%8 of the 8-byte
-// runs read by lanes 2e + (l%16)/8, e = 0..7, so source lane s (group g)
-// reads k-row ks*64 + 32(g/2) + 8h + s/2 at rows base + 16(g%2) + 8(s%2);
-// four reads (h = 0..3) give the lane's 32 k values.
-template <class C, int ROWS>
-__device__ __forceinline__ void frag_tr8(u32x4 (&out)[2], const char *op, uint32_t base, int ks, int lane) {
-    typedef int i32x2 __attribute__((ext_vector_type(2)));
-    constexpr int RB = ROWS;
-    const int g = lane >> 4, s16 = lane & 15;
-    const uint32_t r0 = base + 16 * (g & 1) + 8 * (s16 & 1);
-    uint32_t w[8];
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-        const int p = ks * 64 + 32 * (g >> 1) + 8 * h + (s16 >> 1);
-        const uint32_t off = (uint32_t)p * RB + (((r0 >> 4) ^ (uint32_t)nkc_swizzle<1, ROWS>(p)) << 4) + (r0 & 15);
-        const i32x2 v =
-            __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i32x2 *)(op + off));
-        w[2 * h] = (uint32_t)v[0];
-        w[2 * h + 1] = (uint32_t)v[1];
-    }
-    out[0] = u32x4{w[0], w[1], w[2], w[3]};
-    out[1] = u32x4{w[4], w[5], w[6], w[7]};
-}
-
-// One FP64 MFMA operand fragment from a !KC operand stage: lane l (row
-// base + l%16, group q = l/16) needs k = 8ks + 2q and 8ks + 2q + 1 (one per
-// MFMA of the pair); 16 lanes read 128 consecutive bytes of one k-row.
-template <class C, int ROWS>
-__device__ __forceinline__ u32x4 frag_f64_nkc(const char *op, uint32_t base, int ks, int lane) {
-    constexpr int RB = ROWS * 8;
-    const int q = lane >> 4;
-    const uint32_t r = base + (lane & 15);
-    u32x2 h[2];
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int p = 8 * ks + 2 * q + e;
-        const uint32_t off = (uint32_t)p * RB + (((r >> 1) ^ (uint32_t)nkc_swizzle<8, ROWS>(p)) << 4) + (r & 1) * 8;
-        h[e] = *(const u32x2 *)(op + off);
-    }
-    return u32x4{h[0][0], h[0][1], h[1][0], h[1][1]};
-}
-
-template <class C>
-__device__ __forceinline__ void read_frags(Frag<C> &f, const char *ldsA, const char *ldsB, uint32_t arow,
-                                           uint32_t brow, int ks, int q) {
-    if constexpr (!C::AKC && C::DT == Dt::F64) {
-        const int lane = (int)(arow % 16) + 16 * q;
-#pragma unroll
-        for (int i = 0; i < C::FM; ++i) f.a[i][0] = frag_f64_nkc<C, C::BM>(ldsA, arow - arow % 16 + i * C::MT, ks, lane);
-    } else if constexpr (!C::AKC && C::DT == Dt::F8) {
-        const int lane = (int)(arow % 32) + 32 * q;
-#pragma unroll
-        for (int i = 0; i < C::FM; ++i) frag_tr8<C, C::BM>(f.a[i], ldsA, arow - arow % 32 + i * C::MT, ks, lane);
-    } else if constexpr (!C::AKC) {
-        const int lane = (int)(arow % 32) + 32 * q;
-#pragma unroll
-        for (int i = 0; i < C::FM; ++i) f.a[i][0] = frag_tr<C, C::BM>(ldsA, arow - arow % 32 + i * C::MT, ks, lane);
-    } else {
-#pragma unroll
-        for (int s = 0; s < Frag<C>::CPM; ++s) {
-            const int c = frag_chunk<C>(ks, q, s);
-#pragma unroll
-            for (int i = 0; i < C::FM; ++i) f.a[i][s] = *(const u32x4 *)(ldsA + lds_off(arow + i * C::MT, c));
-        }
-    }
-    if constexpr (!C::BKC && C::DT == Dt::F64) {
-        const int lane = (int)(brow % 16) + 16 * q;
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) f.b[j][0] = frag_f64_nkc<C, C::BN>(ldsB, brow - brow % 16 + j * C::MT, ks, lane);
-    } else if constexpr (!C::BKC && C::DT == Dt::F8) {
-        const int lane = (int)(brow % 32) + 32 * q;
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) frag_tr8<C, C::BN>(f.b[j], ldsB, brow - brow % 32 + j * C::MT, ks, lane);
-    } else if constexpr (!C::BKC) {
-        const int lane = (int)(brow % 32) + 32 * q;
-#pragma unroll
-        for (int j = 0; j < C::FN; ++j) f.b[j][0] = frag_tr<C, C::BN>(ldsB, brow - brow % 32 + j * C::MT, ks, lane);
-    } else {
-#pragma unroll
-        for (int s = 0; s < Frag<C>::CPM; ++s) {
-            const int c = frag_chunk<C>(ks, q, s);
-#pragma unroll
-            for (int j = 0; j < C::FN; ++j) f.b[j][s] = *(const u32x4 *)(ldsB + lds_off(brow + j * C::MT, c));
-        }
-    }
-}
 
 __device__ __forceinline__ double lo_d(const u32x4 &x) { return u2d((uint64_t)x[0] | ((uint64_t)x[1] << 32)); }
 __device__ __forceinline__ double hi_d(const u32x4 &x) { return u2d((uint64_t)x[2] | ((uint64_t)x[3] << 32)); }
 
-// One fragment pair of one 16x16 block, accumulated (16-bit and FP8 types):
-// D = B_frag * A_frag, the transposed block (see the output layout)
+// One fragment pair of one 16x16 block, accumulated.  16-bit and FP8 types:
+// D = B_frag * A_frag, the transposed block (see the output layout).
 template <class C>
 __device__ __forceinline__ void mfma16(typename C::Frag &acc, const u32x4 (&a)[Frag<C>::CPM],
                                        const u32x4 (&b)[Frag<C>::CPM]) {
-    if constexpr (C::DT == Dt::BF16) {
+    if constexpr (C::DT == Dt::F64) {
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(lo_d(a[0]), lo_d(b[0]), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(hi_d(a[0]), hi_d(b[0]), acc, 0, 0, 0);
+    } else if constexpr (C::DT == Dt::BF16) {
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, b[0]),
                                                       __builtin_bit_cast(bf16x8, a[0]), acc, 0, 0, 0);
     } else if constexpr (C::DT == Dt::F16) {
@@ -366,28 +219,7 @@ __device__ __forceinline__ void mfma_step(typename C::Frag (&acc)[C::FM][C::FN],
 #pragma unroll
     for (int i = 0; i < C::FM; ++i)
 #pragma unroll
-        for (int j = 0; j < C::FN; ++j) {
-            const typename C::Frag cin = acc[i][j];
-            if constexpr (C::DT == Dt::F64) {
-                acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(lo_d(f.a[i][0]), lo_d(f.b[j][0]), cin, 0, 0, 0);
-                acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(hi_d(f.a[i][0]), hi_d(f.b[j][0]), acc[i][j], 0, 0, 0);
-            } else if constexpr (C::DT == Dt::BF16) {
-                // D = B_frag * A_frag: the transposed block (see the output layout)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                    __builtin_bit_cast(bf16x8, f.b[j][0]), __builtin_bit_cast(bf16x8, f.a[i][0]), cin, 0, 0, 0);
-            } else if constexpr (C::DT == Dt::F16) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-                    __builtin_bit_cast(f16x8, f.b[j][0]), __builtin_bit_cast(f16x8, f.a[i][0]), cin, 0, 0, 0);
-            } else {
-                const i32x8 av = __builtin_shufflevector(__builtin_bit_cast(i32x4, f.a[i][0]),
-                                                         __builtin_bit_cast(i32x4, f.a[i][1]), 0, 1, 2, 3, 4, 5, 6, 7);
-                const i32x8 bv = __builtin_shufflevector(__builtin_bit_cast(i32x4, f.b[j][0]),
-                                                         __builtin_bit_cast(i32x4, f.b[j][1]), 0, 1, 2, 3, 4, 5, 6, 7);
-                // formats 0/0 = FP8 e4m3 for both operands; E8M0 scales of
-                // 2^0 (127): the per-tensor FP32 scales go into alpha
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(bv, av, cin, 0, 0, 0, 127, 0, 127);
-            }
-        }
+        for (int j = 0; j < C::FN; ++j) mfma16<C>(acc[i][j], f.a[i], f.b[j]);
 }
 
 // ---------------------------------------------------------------------------
@@ -430,16 +262,19 @@ __device__ __forceinline__ void mfma_step(typename C::Frag (&acc)[C::FM][C::FN],
 // spill).
 // ---------------------------------------------------------------------------
 
-// Chunk swizzle of k-row p of a !KC half-tile (HR values per k-row): two
-// 16-lane groups' transpose reads, whose k-rows lie 8 (16-bit) or 16 (FP8)
-// apart, hit every bank once.
+// Chunk swizzle of k-row p of a !KC operand part (HR values per k-row): the
+// lanes that one LDS cycle serves hit every bank once -- two 16-lane groups'
+// transpose reads, whose k-rows lie 8 (16-bit) or 16 (FP8) apart; FP64: 4
+// k-rows two apart x 128 bytes.  The swizzled chunk stays inside its k-row.
 template <int E, int HR>
-__device__ __forceinline__ int half_swizzle(int p) {
-    static_assert(E * HR == 64 || E * HR == 128 || E * HR == 256, "k-row bytes");
-    if constexpr (E * HR == 256) return 4 * (p & 3) ^ 2 * ((p >> 3) & 1);                        // 16-bit, 128 rows
-    else if constexpr (E == 2) return 2 * ((p >> 1) & 1) ^ 4 * ((p >> 3) & 1);                   // 16-bit, 64 rows
-    else if constexpr (E * HR == 128) return 2 * ((p >> 1) & 3) ^ ((p >> 4) & 1);                // FP8, 128 rows
-    else return ((p >> 2) & 1) ^ 2 * ((p >> 4) & 1);                                             // FP8, 64 rows
+__device__ __forceinline__ int kr_swizzle(int p) {
+    constexpr int RB = E * HR;
+    static_assert(E == 8 ? RB >= 256 : RB == 64 || RB == 128 || RB == 256, "k-row bytes");
+    if constexpr (E == 8) return 8 * ((p >> 1) & 1);
+    else if constexpr (RB == 256) return 4 * (p & 3) ^ 2 * ((p >> 3) & 1);                 // 16-bit, 128 rows
+    else if constexpr (E == 2) return 2 * ((p >> 1) & 1) ^ 4 * ((p >> 3) & 1);             // 16-bit, 64 rows
+    else if constexpr (RB == 128) return 2 * ((p >> 1) & 3) ^ ((p >> 4) & 1);              // FP8, 128 rows
+    else return ((p >> 2) & 1) ^ 2 * ((p >> 4) & 1);                                       // FP8, 64 rows
 }
 
 // The global -> LDS loads of one operand: NH parts (PP: the two halves) of HR
@@ -500,9 +335,7 @@ struct OpDma {
             ustep = (int64_t)BK * ld * E;
             pos = w * KR + L / CPR;
             // (the swizzle is the same STEP k-rows on)
-            int c = L % CPR;
-            if constexpr (C::HALVES) c ^= half_swizzle<E, HR>(pos);
-            else c ^= nkc_swizzle<E, HR>(pos);
+            const int c = (L % CPR) ^ kr_swizzle<E, HR>(pos);
 #pragma unroll
             for (int h = 0; h < NH; ++h) voff[h] = h * HR + c * VEC < rows ? pos * ldb + (h * HR * E + c * 16) : OOB;
         }
@@ -545,22 +378,35 @@ struct OpDma {
     }
 };
 
-// One 16x16 MFMA operand fragment of k-step ks from a half-tile buffer of HR
-// rows: lane l feeds row row0 + l % 16 with the k values of lane group l / 16
-// (8 of 32 for 16-bit types, 32 of 128 for FP8).  !KC: as frag_tr / frag_tr8,
-// with a lane group's transpose reads covering its own 16 rows.
+// One MFMA operand fragment of k-step ks from an operand part of HR rows whose
+// block starts at row0.  !KC: ds_read_b64_tr_b16 hands lane l of a 16-lane
+// group element l%4 of the 4-value runs read by lanes 4e + (l%16)/4, e = 0..3,
+// ds_read_b64_tr_b8 byte l%8 of the 8-byte runs read by lanes 2e + (l%16)/8,
+// e = 0..7, so source lane s16 reads k-row s16/4 (s16/2) of the group's at rows
+// 4(s16%4) (8(s16%2)); two reads give the 8 16-bit values, four the 32 FP8 ones.
+// FP64: two 8-byte reads, 16 lanes covering 128 bytes of one k-row.
 template <class C, bool KC, int HR>
-__device__ __forceinline__ void read_half_frag(u32x4 (&out)[Frag<C>::CPM], const char *op, int row0, int ks, int lane) {
+__device__ __forceinline__ void read_frag(u32x4 (&out)[Frag<C>::CPM], const char *op, int row0, int ks, int lane) {
     const int g = lane >> 4, s16 = lane & 15;
     if constexpr (KC) {
 #pragma unroll
         for (int s = 0; s < Frag<C>::CPM; ++s)
             out[s] = *(const u32x4 *)(op + lds_off((uint32_t)(row0 + s16), (uint32_t)(ks * 4 + g + 4 * s)));
+    } else if constexpr (C::DT == Dt::F64) {
+        constexpr int RB = HR * 8;
+        const uint32_t r = (uint32_t)(row0 + s16);
+        u32x2 h[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int p = 8 * ks + 2 * g + e;
+            h[e] = *(const u32x2 *)(op + (uint32_t)p * RB + (((r >> 1) ^ (uint32_t)kr_swizzle<8, HR>(p)) << 4) + (r & 1) * 8);
+        }
+        out[0] = u32x4{h[0][0], h[0][1], h[1][0], h[1][1]};
     } else if constexpr (C::DT == Dt::F8) {
         typedef int i32x2 __attribute__((ext_vector_type(2)));
         // (adding 8 h or 64 to the k-row leaves its swizzle alone)
         const int r0 = row0 + 8 * (s16 & 1), p0 = 16 * g + (s16 >> 1);
-        const char *const src = op + p0 * HR + (((r0 >> 4) ^ half_swizzle<1, HR>(p0)) << 4) + (r0 & 15);
+        const char *const src = op + p0 * HR + (((r0 >> 4) ^ kr_swizzle<1, HR>(p0)) << 4) + (r0 & 15);
         uint32_t v[8];
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
@@ -574,7 +420,7 @@ __device__ __forceinline__ void read_half_frag(u32x4 (&out)[Frag<C>::CPM], const
     } else {
         typedef short s16x4 __attribute__((ext_vector_type(4)));
         const int r0 = row0 + 4 * (s16 & 3), p0 = 8 * g + (s16 >> 2);
-        const char *const src = op + p0 * HR * 2 + (((r0 >> 3) ^ half_swizzle<2, HR>(p0)) << 4) + (r0 & 7) * 2;
+        const char *const src = op + p0 * HR * 2 + (((r0 >> 3) ^ kr_swizzle<2, HR>(p0)) << 4) + (r0 & 7) * 2;
         u32x2 v[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -599,7 +445,7 @@ struct PpState {
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int i = 0; i < FMH; ++i)
-                read_half_frag<C, C::AKC, HM>(a[i][ks], op, wm * (C::WTM / 2) + i * C::MT, ks, lane);
+                read_frag<C, C::AKC, HM>(a[i][ks], op, wm * (C::WTM / 2) + i * C::MT, ks, lane);
     }
     template <int H>
     __device__ __forceinline__ void read_b(const char *op, int wn, int lane) {
@@ -607,7 +453,7 @@ struct PpState {
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int j = 0; j < FNH; ++j)
-                read_half_frag<C, C::BKC, HN>(b[H][j][ks], op, wn * (C::WTN / 2) + j * C::MT, ks, lane);
+                read_frag<C, C::BKC, HN>(b[H][j][ks], op, wn * (C::WTN / 2) + j * C::MT, ks, lane);
     }
     template <int HA, int HB>
     __device__ __forceinline__ void mfma(typename C::Frag (&acc)[C::FM][C::FN]) const {
@@ -783,8 +629,8 @@ struct HalfState {
         for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
             for (int i = 0; i < (OP == 0 ? FA : FB); ++i) {
-                if constexpr (OP == 0) read_half_frag<C, C::AKC, HR>(a[H][i][ks], op, w * (C::WTM / 2) + i * C::MT, ks, lane);
-                else read_half_frag<C, C::BKC, HR>(b[H][i][ks], op, w * (C::WTN / 2) + i * C::MT, ks, lane);
+                if constexpr (OP == 0) read_frag<C, C::AKC, HR>(a[H][i][ks], op, w * (C::WTM / 2) + i * C::MT, ks, lane);
+                else read_frag<C, C::BKC, HR>(b[H][i][ks], op, w * (C::WTN / 2) + i * C::MT, ks, lane);
             }
     }
     template <int HA, int HB>
@@ -898,48 +744,66 @@ struct RingState {
     static constexpr int DPK = OpDma<C, C::AKC, C::BM, 1>::NL + OpDma<C, C::BKC, C::BN, 1>::NL;   // loads per wave per k-tile
 };
 
+// a wave's fragments of k-step ks of the k-tile at `st`
+template <class C>
+__device__ __forceinline__ void read_frags(Frag<C> &f, const char *st, int wm, int wn, int ks, int lane) {
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i) read_frag<C, C::AKC, C::BM>(f.a[i], st, wm * C::WTM + i * C::MT, ks, lane);
+#pragma unroll
+    for (int j = 0; j < C::FN; ++j) read_frag<C, C::BKC, C::BN>(f.b[j], st + C::A_BYTES, wn * C::WTN + j * C::MT, ks, lane);
+}
+
 // One k-tile: operands at cur, the next k-tile at nx, the loads of k-tile
 // t + LA into ld.  WHOLE: that one lies inside the segment and the matrices
 // (abase, bbase: its addresses, advanced).
 template <class C, bool WHOLE>
 __device__ __forceinline__ void ktile_ring(const RingState<C> &st, Frag<C> (&f)[2],
                                            typename C::Frag (&acc)[C::FM][C::FN], const char *cur, const char *nx,
-                                           char *ld, int t, int t1, uint32_t arow, uint32_t brow, int q,
-                                           uint64_t &abase, uint64_t &bbase) {
+                                           char *ld, int t, int t1, int wm, int wn, int lane, uint64_t &abase,
+                                           uint64_t &bbase) {
     constexpr int NSUB = Frag<C>::NSUB, LA = C::NSTAGE - 1;
     const bool live = WHOLE || t + LA < t1;
-    static_for<NSUB>([&](auto kk) {
-        constexpr int ks = decltype(kk)::value;
-        if constexpr (ks + 1 == NSUB) {
-            // k-tile t + 1 has landed; up to LA - 1 newer ones may be in flight
-            if constexpr (WHOLE) wait_loads_lds<(LA - 1) * RingState<C>::DPK>();
-            else wait_newer<LA - 1, RingState<C>::DPK>(t1 - 2 - t);
-            plain_barrier();
-        }
-        constexpr int nks = (ks + 1) % NSUB;
-        const char *const src = ks + 1 < NSUB ? cur : nx;
-        read_frags<C>(f[(ks + 1) & 1], src, src + C::A_BYTES, arow, brow, nks, q);
-        if constexpr (ks == 0) {
+    auto loads = [&](int op) {
+        if (op == 0) {
             if (live) st.da.template issue<0, WHOLE>(ld, t + LA, true, abase);
             if constexpr (WHOLE) abase += st.da.ustep;
-        }
-        if constexpr (ks == (NSUB > 2 ? 1 : 0)) {
+        } else {
             if (live) st.db.template issue<0, WHOLE>(ld + C::A_BYTES, t + LA, true, bbase);
             if constexpr (WHOLE) bbase += st.db.ustep;
         }
-        mfma_step<C>(acc, f[ks & 1]);
-    });
+    };
+    auto landed = [&]() {
+        // k-tile t + 1 has landed; up to LA - 1 newer ones may be in flight
+        if constexpr (WHOLE) wait_loads_lds<(LA - 1) * RingState<C>::DPK>();
+        else wait_newer<LA - 1, RingState<C>::DPK>(t1 - 2 - t);
+        plain_barrier();
+    };
+    if constexpr (NSUB == 1) {
+        loads(0);
+        loads(1);
+        mfma_step<C>(acc, f[0]);
+        landed();
+        read_frags<C>(f[0], nx, wm, wn, 0, lane);
+    } else {
+        static_assert(NSUB % 2 == 0, "fragment double buffer needs an even step count");
+        static_for<NSUB>([&](auto kk) {
+            constexpr int ks = decltype(kk)::value;
+            if constexpr (ks + 1 == NSUB) landed();
+            read_frags<C>(f[(ks + 1) & 1], ks + 1 < NSUB ? cur : nx, wm, wn, (ks + 1) % NSUB, lane);
+            if constexpr (ks == 0) {
+                loads(0);
+                loads(1);
+            }
+            mfma_step<C>(acc, f[ks & 1]);
+        });
+    }
 }
 
 template <class C>
 __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int it0, int it1,
                                          typename C::Frag (&acc)[C::FM][C::FN], char *lds, int tid) {
-    static_assert(Frag<C>::NSUB % 2 == 0, "fragment double buffer needs an even step count");
     constexpr int LA = C::NSTAGE - 1, RING = C::NSTAGE * C::STAGE;
     const int lane = tid & 63, wave = tid >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
-    const int q = lane / C::MT;
-    const uint32_t arow = (uint32_t)(wm * C::WTM + (lane % C::MT));
-    const uint32_t brow = (uint32_t)(wn * C::WTN + (lane % C::MT));
     RingState<C> st;
     st.da.init(P.A, P.lda, tm * C::BM, P.m, P.k, tid);
     st.db.init(P.B, P.ldb, tn * C::BN, P.n, P.k, tid);
@@ -958,7 +822,7 @@ __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int i
     wait_newer<LA - 1, RingState<C>::DPK>(it1 - 1 - it0);
     plain_barrier();
     Frag<C> f[2];
-    read_frags<C>(f[0], lds, lds + C::A_BYTES, arow, brow, 0, q);
+    read_frags<C>(f[0], lds, wm, wn, 0, lane);
     int t = it0;
     int cur = 0, nx = C::STAGE % RING, ld = LA * C::STAGE;      // byte offsets of the buffers in turn
     uint64_t ab = (uint64_t)st.da.ub + (it0 + LA) * st.da.ustep, bb = (uint64_t)st.db.ub + (it0 + LA) * st.db.ustep;
@@ -973,16 +837,16 @@ __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int i
             static_for<C::NSTAGE>([&](auto pp) {
                 constexpr int p = decltype(pp)::value;
                 ktile_ring<C, true>(st, f, acc, lds + p * C::STAGE, lds + (p + 1) % C::NSTAGE * C::STAGE,
-                                    lds + (p + LA) % C::NSTAGE * C::STAGE, t + p, it1, arow, brow, q, ab, bb);
+                                    lds + (p + LA) % C::NSTAGE * C::STAGE, t + p, it1, wm, wn, lane, ab, bb);
             });
     } else {
         for (; t + LA < full; ++t) {
-            ktile_ring<C, true>(st, f, acc, lds + cur, lds + nx, lds + ld, t, it1, arow, brow, q, ab, bb);
+            ktile_ring<C, true>(st, f, acc, lds + cur, lds + nx, lds + ld, t, it1, wm, wn, lane, ab, bb);
             turn();
         }
     }
     for (; t < it1; ++t) {
-        ktile_ring<C, false>(st, f, acc, lds + cur, lds + nx, lds + ld, t, it1, arow, brow, q, ab, bb);
+        ktile_ring<C, false>(st, f, acc, lds + cur, lds + nx, lds + ld, t, it1, wm, wn, lane, ab, bb);
         turn();
     }
     __syncthreads();      // every wave is done with the buffers, which the epilogue uses next
@@ -992,10 +856,9 @@ __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int i
 // accumulator <-> (row, col) and the epilogue
 // ---------------------------------------------------------------------------
 // Output layout of a fragment.
-// 32x32 and 16x16 blocks of f16/bf16/f8: the MFMAs compute D = B_frag *
-// A_frag, the transposed block, so lane l holds C row (l % MT) of the block
-// and, in accumulator register 4g+e, column 8g + 4(l / MT) + e: four
-// consecutive columns per group g (16x16: one group), stored as one vector.
+// f16/bf16/f8: the MFMAs compute D = B_frag * A_frag, the transposed block, so
+// lane l holds C row (l % 16) of the block and, in accumulator register e,
+// column 4(l / 16) + e: four consecutive columns, stored as one vector.
 // 16x16 f64 blocks: D = A_frag * B_frag; lane l holds column (l % 16) and,
 // in register r, row 4r + (l / 16).
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
@@ -1100,12 +963,6 @@ __device__ __forceinline__ typename C::Frag load_partial_frag(const char *slot, 
                                                                              0, CPOL_DEVICE));
     if constexpr (PL::CPF == 1) {
         return __builtin_bit_cast(f32x4, c[0]);
-    } else if constexpr (PL::PER == 4) {
-        const f32x8 lo = __builtin_shufflevector(__builtin_bit_cast(f32x4, c[0]), __builtin_bit_cast(f32x4, c[1]), 0,
-                                                 1, 2, 3, 4, 5, 6, 7);
-        const f32x8 hi = __builtin_shufflevector(__builtin_bit_cast(f32x4, c[2]), __builtin_bit_cast(f32x4, c[3]), 0,
-                                                 1, 2, 3, 4, 5, 6, 7);
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
     } else {
         return __builtin_shufflevector(__builtin_bit_cast(f64x2, c[0]), __builtin_bit_cast(f64x2, c[1]), 0, 1, 2, 3);
     }
@@ -1172,12 +1029,6 @@ struct FixStage {
         }
         if constexpr (PL::CPF == 1) {
             return __builtin_bit_cast(f32x4, c[0]);
-        } else if constexpr (PL::PER == 4) {
-            const f32x8 lo = __builtin_shufflevector(__builtin_bit_cast(f32x4, c[0]), __builtin_bit_cast(f32x4, c[1]),
-                                                     0, 1, 2, 3, 4, 5, 6, 7);
-            const f32x8 hi = __builtin_shufflevector(__builtin_bit_cast(f32x4, c[2]), __builtin_bit_cast(f32x4, c[3]),
-                                                     0, 1, 2, 3, 4, 5, 6, 7);
-            return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
         } else {
             return __builtin_shufflevector(__builtin_bit_cast(f64x2, c[0]), __builtin_bit_cast(f64x2, c[1]), 0, 1, 2,
                                            3);
@@ -1213,7 +1064,7 @@ __device__ __forceinline__ void fix_phase(bool staged, const char *slots, int p0
     }
 }
 
-// Epilogue of a tile with no partial sums to add (32x32 blocks, C rows
+// Epilogue of a tile with no partial sums to add (C rows
 // 16-byte aligned): the fragments pass through the idle MAC-loop LDS buffers
 // so that C is written in whole rows.  Straight from the MFMA layout a store
 // instruction covers 32 rows with 32 bytes each (16 with a 16-bit C), one
@@ -1532,7 +1383,7 @@ struct Spread {
                 }
             }
         } else {
-            // 32x32 blocks: four consecutive columns of one row
+            // four consecutive columns of one row
             const f32x4 v = __builtin_bit_cast(f32x4, raw);
             const int row = tm * C::BM + C::frow(wm, fi) + (lane % C::MT);
             const int col = tn * C::BN + C::fcol(wn, fj) + 8 * sc + 4 * (lane / C::MT);
@@ -1574,7 +1425,7 @@ struct Spread {
             row = tm * C::BM + wm * C::WTM + fi * 16 + 4 * (2 * sc + e) + (lane >> 4);
             col = tn * C::BN + wn * C::WTN + fj * 16 + (lane & 15);
         } else {
-            // 32x32 blocks: four consecutive columns of one row
+            // four consecutive columns of one row
             row = tm * C::BM + C::frow(wm, fi) + (lane % C::MT);
             col = tn * C::BN + C::fcol(wn, fj) + 8 * sc + 4 * (lane / C::MT) + e;
         }
