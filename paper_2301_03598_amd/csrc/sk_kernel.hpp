@@ -890,26 +890,33 @@ __device__ __forceinline__ void put_c(char *p, Acc v) {
 
 template <int CT> struct CBytes { static constexpr int v = CT == SK_F64 ? 8 : (CT == SK_F32 ? 4 : 2); };
 
+// Four consecutive elements of C.
+template <int CT, class Acc>
+__device__ __forceinline__ void load4(const char *p, Acc (&v)[4]) {
+    if constexpr (CT == SK_F64) {
+        const f64x4 o = *(const f64x4 *)p;
+        for (int e = 0; e < 4; ++e) v[e] = (Acc)o[e];
+    } else if constexpr (CT == SK_F32) {
+        const u32x4 o = *(const u32x4 *)p;
+        for (int e = 0; e < 4; ++e) v[e] = (Acc)u2f(o[e]);
+    } else {
+        const u32x2 o = *(const u32x2 *)p;
+        for (int e = 0; e < 4; ++e) {
+            const uint16_t h = (uint16_t)(o[e >> 1] >> ((e & 1) * 16));
+            v[e] = (Acc)(CT == SK_F16 ? (float)__builtin_bit_cast(_Float16, h) : bf16_to_f32(h));
+        }
+    }
+}
+
 // Four consecutive outputs of one row, alpha*acc (+ beta*C), rounded once.
 template <int CT, class Acc>
 __device__ __forceinline__ void put4(char *p, const Acc (&v)[4], Acc beta, bool rd) {
     constexpr int EB = CBytes<CT>::v;
     Acc w[4];
     if (rd) {
-        if constexpr (CT == SK_F64) {
-            const f64x4 o = *(const f64x4 *)p;
-            for (int e = 0; e < 4; ++e) w[e] = v[e] + beta * (Acc)o[e];
-        } else if constexpr (CT == SK_F32) {
-            const u32x4 o = *(const u32x4 *)p;
-            for (int e = 0; e < 4; ++e) w[e] = v[e] + beta * (Acc)u2f(o[e]);
-        } else {
-            const u32x2 o = *(const u32x2 *)p;
-            for (int e = 0; e < 4; ++e) {
-                const uint16_t h = (uint16_t)(o[e >> 1] >> ((e & 1) * 16));
-                float f = CT == SK_F16 ? (float)__builtin_bit_cast(_Float16, h) : bf16_to_f32(h);
-                w[e] = v[e] + beta * (Acc)f;
-            }
-        }
+        Acc o[4];
+        load4<CT, Acc>(p, o);
+        for (int e = 0; e < 4; ++e) w[e] = v[e] + beta * o[e];
     } else {
         for (int e = 0; e < 4; ++e) w[e] = v[e];
     }
@@ -1064,82 +1071,167 @@ __device__ __forceinline__ void fix_phase(bool staged, const char *slots, int p0
     }
 }
 
-// Epilogue of a tile with no partial sums to add (C rows
-// 16-byte aligned): the fragments pass through the idle MAC-loop LDS buffers
-// so that C is written in whole rows.  Straight from the MFMA layout a store
-// instruction covers 32 rows with 32 bytes each (16 with a 16-bit C), one
-// write request per row; after the transpose a wave's instruction covers
-// 1 KiB of consecutive bytes (512 with a 16-bit C), a few whole 128-byte
-// lines, which makes small-k GEMMs (output-write bound) several times
-// cheaper.  The arithmetic per element is that of store_tile_t: alpha * acc,
-// then + beta * C, rounded once.  Bands of 2 x 32 rows (32 per wave row); each padded LDS row (BN floats + 16 bytes) starts
-// 4 banks after the previous one, so the rows of a fragment write land in
-// distinct banks.  Rows and columns past the edge of C are not stored.
+// Epilogue of a tile with no partial sums to add: the fragments pass through
+// the idle MAC-loop LDS buffers so that C is written in whole rows.  Straight
+// from the MFMA layout a store instruction covers 16 rows with 64 bytes each
+// (32 with a 16-bit C), a write request per row; after the transpose a wave's
+// instruction covers consecutive bytes: 1 KiB (512 with a 16-bit C), or, where
+// C's rows are not 16-byte aligned, 64 consecutive elements of one row.  The
+// arithmetic per element is that of store_tile_t: alpha * acc, then + beta *
+// C, rounded once.  Bands of 2 x 32 rows (32 per wave row) in two LDS regions
+// by turns; chunk c of a row lies at c ^ (row % 16), so the 16 rows of a
+// fragment write land in distinct banks.  Rows and columns past the edge of C
+// are not stored.
+//
+// One barrier per band: a band's writes follow the barrier of the band before
+// it, which every wave passes with its reads of the band before that done.
+// The barriers wait for LDS accesses only: a __syncthreads would have each
+// band wait for the stores of the one before to reach memory.
+//
+// The common case, whole aligned rows and no old C, is unrolled over the
+// bands; the rest takes one rolled piece of code with only the bands' fragment
+// writes (accumulators are indexed by constants) unrolled.  A tile runs this
+// once, so both its waits and its length are latency.  Unrolled throughout,
+// with the __syncthreads: the FP16 256x256 kernel is 149 KB, this way 66;
+// 4096x4096x64 (one tile per CU) took 13.4 us, now 11.9; 8192x8192x128 58.7, 53.1;
+// 128x128 tiles, 2048x2048x512 into FP32 11.9, 11.2; 2040x3000x520 17.8, 16.9.
 template <class C, int CT>
 __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn,
-                                                const typename C::Frag (&acc)[C::FM][C::FN], int tid,
-                                                char *lds, bool interior) {
+                                                const typename C::Frag (&acc)[C::FM][C::FN], int tid, char *lds,
+                                                bool interior) {
     using Acc = typename C::Acc;
     constexpr int EB = CBytes<CT>::v;
-    constexpr int G = C::FRAG_N / 4;                  // column groups per fragment
-    constexpr int RS = C::BN * 4 + 16;                // padded LDS row
+    constexpr int RS = C::BN * 4;                     // LDS row
     constexpr int Q = C::BN / 4;                      // 16-byte chunks per row
     constexpr int BR = 32, FB = BR / C::MT;           // band rows per wave row, in FB fragment rows
+    constexpr int NB = C::FM / FB;                    // bands
     constexpr int NCH = C::WGM * BR * Q / C::THREADS; // chunks per thread per band
-    static_assert(C::WGM == 2 && C::WGM * BR * RS <= C::LDS, "a band fits the k-tile buffers");
-    static_assert((C::WGM * BR * Q) % C::THREADS == 0, "whole chunks per thread");
+    constexpr int RPU = C::THREADS / Q;               // rows between a thread's chunks
+    constexpr int REGION = C::WGM * BR * RS;
+    static_assert(C::WGM == 2 && 2 * REGION <= C::LDS && Q >= 16, "two bands fit the k-tile buffers");
+    static_assert(C::THREADS % Q == 0 && BR % RPU == 0 && NCH % 2 == 0, "whole rows per round");
     const int lane = tid & 63, wave = tid >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
     const Acc alpha = (Acc)P.alpha, beta = (Acc)P.beta;
     const bool rd = P.beta != 0.0;
-    static_for<C::FM / FB>([&](auto ii) {
-        constexpr int i = decltype(ii)::value * FB;   // the band's first fragment row
-        __syncthreads();                              // LDS free: MAC-loop reads, previous band
+    auto write_band = [&](auto bb, char *reg) {
+        constexpr int i = decltype(bb)::value * FB;
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb) {
-            const int lr = fb * C::MT + lane % C::MT;
-            char *const wr = lds + (wm * BR + lr) * RS + (C::fcol(wn, 0) + 4 * (lane / C::MT)) * 4;
+            char *const wr = reg + (wm * BR + fb * C::MT + lane % C::MT) * RS;
 #pragma unroll
             for (int j = 0; j < C::FN; ++j) {
-                // an opaque copy where it is used, as in fix_frag: the copies
-                // of all fragments are not hoisted out of the accumulator
-                // registers
+                // an opaque copy where it is used, as in fix_frag: the products
+                // of all fragments are not formed ahead
                 typename C::Frag f = acc[i + fb][j];
                 asm volatile("" : "+v"(f));
+                f32x4 v;
 #pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    f32x4 v;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = alpha * f[4 * g + e];
-                    *(f32x4 *)(wr + (C::fcol(0, j) + 8 * g) * 4) = v;
-                }
+                for (int e = 0; e < 4; ++e) v[e] = alpha * f[e];
+                *(f32x4 *)(wr + ((C::fcol(wn, j) / 4 + lane / C::MT) ^ (lane % C::MT)) * 16) = v;
             }
         }
-        __syncthreads();
+    };
+    const int br0 = tid / Q;
+    auto staged = [&](const char *reg, int u) {
+        return *(const f32x4 *)(reg + (br0 + u * RPU) * RS + ((tid % Q) ^ ((br0 + u * RPU) % 16)) * 16);
+    };
+    if (P.c_vec && interior && !rd) {
+        char *const q = (char *)P.C + ((int64_t)(tm * C::BM + br0) * P.ldc + tn * C::BN + 4 * (tid % Q)) * EB;
+        static_for<NB>([&](auto bb) {
+            constexpr int band = decltype(bb)::value;
+            char *const reg = lds + (band & 1) * REGION;
+            write_band(bb, reg);
+            wait_lds();
+            plain_barrier();
 #pragma unroll
-        for (int u = 0; u < NCH; ++u) {
-            const int c = tid + u * C::THREADS;
-            const int br = c / Q, c4 = c % Q;         // band row, chunk in the row
-            const f32x4 v = *(const f32x4 *)(lds + br * RS + c4 * 16);
-            const int row = tm * C::BM + C::frow(br / BR, i) + br % BR;
-            const int col = tn * C::BN + 4 * c4;
-            const Acc a[4] = {v[0], v[1], v[2], v[3]};
-            char *const q = (char *)P.C + ((int64_t)row * P.ldc + col) * EB;
-            if (interior || (row < P.m && col + 4 <= P.n)) {
-                put4<CT, Acc>(q, a, beta, rd);
-            } else if (row < P.m) {
-                // the last chunk of a row that ends inside it
+            for (int u = 0; u < NCH; ++u) {
+                const int row = C::frow(u / (NCH / 2), band * FB) + u % (NCH / 2) * RPU;
+                const f32x4 v = staged(reg, u);
+                const Acc w[4] = {v[0], v[1], v[2], v[3]};
+                put4<CT, Acc>(q + (int64_t)row * P.ldc * EB, w, beta, false);
+            }
+        });
+        wait_lds();
+        plain_barrier();                              // LDS free for the next unit's loads
+        return;
+    }
+#pragma unroll 1
+    for (int band = 0; band < NB; ++band) {
+        char *const reg = lds + (band & 1) * REGION;
+        static_for<NB>([&](auto bb) {
+            if (band == decltype(bb)::value) write_band(bb, reg);
+        });
+        wait_lds();
+        plain_barrier();
+        // the band's first row in C for each wave row
+        const int r0 = tm * C::BM + C::frow(0, band * FB), r1 = tm * C::BM + C::frow(1, band * FB);
+        if (P.c_vec) {
+            const int col = tn * C::BN + 4 * (tid % Q);
+            char *const q0 = (char *)P.C + ((int64_t)(r0 + br0) * P.ldc + col) * EB;
+            char *const q1 = (char *)P.C + ((int64_t)(r1 + br0) * P.ldc + col) * EB;
+            const int64_t step = (int64_t)RPU * P.ldc * EB;
+            // C's old values (a short batch ahead of their use), edges
+            constexpr int UB = NCH < 4 ? NCH : 4;
+#pragma unroll 1
+            for (int ub = 0; ub < NCH; ub += UB) {
+                Acc old[UB][4];
+                bool full[UB];
+                char *q[UB];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (col + e < P.n) {
-                        Acc w = a[e];
-                        if (rd) w = w + beta * load_c<CT, Acc>(q + e * EB);
-                        put_c<CT, Acc>(q + e * EB, w);
+                for (int u = 0; u < UB; ++u) {
+                    const int x = ub + u, rr = (x < NCH / 2 ? r0 : r1) + br0 + x % (NCH / 2) * RPU;
+                    q[u] = (x < NCH / 2 ? q0 : q1) + x % (NCH / 2) * step;
+                    full[u] = rr < P.m && col + 4 <= P.n;
+                    if (full[u] && rd) load4<CT, Acc>(q[u], old[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    const int x = ub + u, rr = (x < NCH / 2 ? r0 : r1) + br0 + x % (NCH / 2) * RPU;
+                    const f32x4 v = staged(reg, x);
+                    Acc w[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = full[u] && rd ? v[e] + beta * old[u][e] : v[e];
+                    if (full[u]) {
+                        put4<CT, Acc>(q[u], w, beta, false);
+                    } else if (rr < P.m) {
+                        // the last chunk of a row that ends inside it
+                        for (int e = 0; e < 4 && col + e < P.n; ++e) {
+                            Acc y = e == 0 ? w[0] : e == 1 ? w[1] : e == 2 ? w[2] : w[3];
+                            if (rd) y = y + beta * load_c<CT, Acc>(q[u] + e * EB);
+                            put_c<CT, Acc>(q[u] + e * EB, y);
+                        }
                     }
                 }
             }
+        } else {
+            // one element per lane and row piece
+            constexpr int NE = C::WGM * BR * C::BN / C::THREADS, UB = 8;
+            static_assert(NE % UB == 0, "whole batches of elements");
+#pragma unroll 1
+            for (int ub = 0; ub < NE; ub += UB) {
+                Acc old[UB];
+                bool in[UB];
+                char *q[UB];
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    const int c = tid + (ub + u) * C::THREADS, br = c / C::BN, col = tn * C::BN + c % C::BN;
+                    const int row = (br < BR ? r0 : r1) + br % BR;
+                    q[u] = (char *)P.C + ((int64_t)row * P.ldc + col) * EB;
+                    in[u] = row < P.m && col < P.n;
+                    if (in[u] && rd) old[u] = load_c<CT, Acc>(q[u]);
+                }
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    const int c = tid + (ub + u) * C::THREADS, br = c / C::BN, e = c % C::BN;
+                    Acc w = *(const float *)(reg + br * RS + ((e / 4) ^ (br % 16)) * 16 + e % 4 * 4);
+                    if (rd) w = w + beta * old[u];
+                    if (in[u]) put_c<CT, Acc>(q[u], w);
+                }
+            }
         }
-    });
-    __syncthreads();                                  // LDS free for the next unit's loads
+    }
+    wait_lds();
+    plain_barrier();                                  // LDS free for the next unit's loads
 }
 
 // C_tile = alpha * (acc + partials of slots [p0, p1]) + beta * C_tile (C read
@@ -1184,16 +1276,13 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
         });
         return;
     }
-    // (16-bit inputs only, from the 128x128 tile on: the staging's registers
-    // would cost the 64x64 Stream-K kernel a wave per SIMD, and with it the
-    // FP8 kernels' MAC loops measured 3 % slower at large k)
-    if constexpr (C::BM >= 128 && (C::DT != Dt::F8 || C::PP)) {
-        if (P.c_vec && p0 > p1) {
-            // whole rows through the LDS, edge tiles included (the flags are
-            // uniform over the workgroup)
-            store_tile_rows<C, CT>(P, tm, tn, acc, tid, lds, interior);
-            return;
-        }
+    // whole rows through the LDS, edge tiles included (the flags are uniform
+    // over the workgroup); not on the 64x64 tile, where it measures even with
+    // aligned rows and
+    // 5 % slower without
+    if (C::BM >= 128 && p0 > p1) {
+        store_tile_rows<C, CT>(P, tm, tn, acc, tid, lds, interior);
+        return;
     }
     const int rowl = tm * C::BM + C::frow(wm, 0) + (lane % C::MT);
     const int coll = tn * C::BN + C::fcol(wn, 0) + 4 * (lane / C::MT);
@@ -1237,11 +1326,10 @@ __device__ __forceinline__ void store_tile(const Problem &P, int tm, int tn,
     if constexpr (C::DT == Dt::F64) {
         store_tile_t<C, SK_F64>(P, tm, tn, acc, tid, slots, p0, p1, lds);
     } else {
-        switch (P.c_type) {
-        case SK_F32: store_tile_t<C, SK_F32>(P, tm, tn, acc, tid, slots, p0, p1, lds); break;
-        case SK_F16: store_tile_t<C, SK_F16>(P, tm, tn, acc, tid, slots, p0, p1, lds); break;
-        default: store_tile_t<C, SK_BF16>(P, tm, tn, acc, tid, slots, p0, p1, lds); break;
-        }
+        // the two output types an input type allows
+        constexpr int CH = C::DT == Dt::F16 ? SK_F16 : SK_BF16;
+        if (P.c_type == SK_F32) store_tile_t<C, SK_F32>(P, tm, tn, acc, tid, slots, p0, p1, lds);
+        else store_tile_t<C, CH>(P, tm, tn, acc, tid, slots, p0, p1, lds);
     }
     // the staged fixup used this wave's LDS regions: keep the next unit's
     // loads out until every wave is done with them
@@ -1521,11 +1609,9 @@ struct Spread {
         if constexpr (C::DT == Dt::F64) {
             reduce_t<SK_F64>(p, P, tm, tn, f, l, x, lds, tid);
         } else {
-            switch (P.c_type) {
-            case SK_F32: reduce_t<SK_F32>(p, P, tm, tn, f, l, x, lds, tid); break;
-            case SK_F16: reduce_t<SK_F16>(p, P, tm, tn, f, l, x, lds, tid); break;
-            default: reduce_t<SK_BF16>(p, P, tm, tn, f, l, x, lds, tid); break;
-            }
+            constexpr int CH = C::DT == Dt::F16 ? SK_F16 : SK_BF16;
+            if (P.c_type == SK_F32) reduce_t<SK_F32>(p, P, tm, tn, f, l, x, lds, tid);
+            else reduce_t<CH>(p, P, tm, tn, f, l, x, lds, tid);
         }
     }
 };
