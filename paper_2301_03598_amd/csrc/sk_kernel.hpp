@@ -861,11 +861,9 @@ __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int i
 // column 4(l / 16) + e: four consecutive columns, stored as one vector.
 // 16x16 f64 blocks: D = A_frag * B_frag; lane l holds column (l % 16) and,
 // in register r, row 4r + (l / 16).
+// round to nearest even, NaNs quieted: the conversion instruction
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);   // quiet NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+    return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
@@ -925,11 +923,9 @@ __device__ __forceinline__ void put4(char *p, const Acc (&v)[4], Acc beta, bool 
     } else if constexpr (CT == SK_F32) {
         *(u32x4 *)p = u32x4{f2u((float)w[0]), f2u((float)w[1]), f2u((float)w[2]), f2u((float)w[3])};
     } else {
-        uint32_t h[4];
-        for (int e = 0; e < 4; ++e)
-            h[e] = CT == SK_F16 ? (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(float)w[e])
-                                : (uint32_t)f32_to_bf16_rne((float)w[e]);
-        *(u32x2 *)p = u32x2{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
+        typedef std::conditional_t<CT == SK_F16, _Float16, __bf16> H;
+        typedef H h4 __attribute__((ext_vector_type(4)));
+        *(h4 *)p = h4{(H)(float)w[0], (H)(float)w[1], (H)(float)w[2], (H)(float)w[3]};
     }
     (void)EB;
 }
@@ -1088,13 +1084,16 @@ __device__ __forceinline__ void fix_phase(bool staged, const char *slots, int p0
 // The barriers wait for LDS accesses only: a __syncthreads would have each
 // band wait for the stores of the one before to reach memory.
 //
-// The common case, whole aligned rows and no old C, is unrolled over the
-// bands; the rest takes one rolled piece of code with only the bands' fragment
-// writes (accumulators are indexed by constants) unrolled.  A tile runs this
-// once, so both its waits and its length are latency.  Unrolled throughout,
-// with the __syncthreads: the FP16 256x256 kernel is 149 KB, this way 66;
-// 4096x4096x64 (one tile per CU) took 13.4 us, now 11.9; 8192x8192x128 58.7, 53.1;
-// 128x128 tiles, 2048x2048x512 into FP32 11.9, 11.2; 2040x3000x520 17.8, 16.9.
+// The bands are unrolled, in one form each for interior tiles, for edges and
+// for old values of C, and in one for rows that are not aligned.  A tile runs
+// this once, so its waits and its instructions are latency: a rolled loop over
+// the bands that served edges, old values and unaligned rows at once added 2
+// us to a tile (172x192x1072 FP8, four 128x128 tiles, 12.3 us; unrolled 8.0).
+// Before (__syncthreads around each band, BF16 rounded in integer steps) and
+// now, us: FP16 4096x4096x64 (one 256x256 tile per CU) 13.5, 12.1; BF16 17.2,
+// 12.2; BF16 8192x8192x128 70.7, 51.6; FP16 128x128 tiles: 2040x3000x520 17.8,
+// 15.4, unaligned rows of FP32 (2041x3001x520) 26.4, 22.5; 8192x8191x128
+// 125.5, 80.2.
 template <class C, int CT>
 __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn,
                                                 const typename C::Frag (&acc)[C::FM][C::FN], int tid, char *lds,
@@ -1113,6 +1112,10 @@ __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn
     const int lane = tid & 63, wave = tid >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
     const Acc alpha = (Acc)P.alpha, beta = (Acc)P.beta;
     const bool rd = P.beta != 0.0;
+    // (opaque: its multiples are formed here, not kept in registers through
+    // the MAC loops)
+    int64_t pitch = (int64_t)P.ldc * EB;
+    asm volatile("" : "+s"(pitch));
     auto write_band = [&](auto bb, char *reg) {
         constexpr int i = decltype(bb)::value * FB;
 #pragma unroll
@@ -1135,101 +1138,90 @@ __device__ __forceinline__ void store_tile_rows(const Problem &P, int tm, int tn
     auto staged = [&](const char *reg, int u) {
         return *(const f32x4 *)(reg + (br0 + u * RPU) * RS + ((tid % Q) ^ ((br0 + u * RPU) % 16)) * 16);
     };
-    if (P.c_vec && interior && !rd) {
-        char *const q = (char *)P.C + ((int64_t)(tm * C::BM + br0) * P.ldc + tn * C::BN + 4 * (tid % Q)) * EB;
-        static_for<NB>([&](auto bb) {
-            constexpr int band = decltype(bb)::value;
-            char *const reg = lds + (band & 1) * REGION;
-            write_band(bb, reg);
-            wait_lds();
-            plain_barrier();
+    if (P.c_vec) {
+        // EDGE: rows and chunks past the edge are left out; RD: C's old
+        // values, loaded ahead of the barrier
+        auto bands = [&](auto edge, auto read) {
+            constexpr bool EDGE = decltype(edge)::value, RD = decltype(read)::value;
+            const int row0 = tm * C::BM + br0, col = tn * C::BN + 4 * (tid % Q);
+            const int rows = !EDGE ? 0 : col + 4 <= P.n ? P.m - row0 : 0;
+            char *const q = (char *)P.C + row0 * pitch + (int64_t)col * EB;
+            static_for<NB>([&](auto bb) {
+                constexpr int band = decltype(bb)::value;
+                char *const reg = lds + (band & 1) * REGION;
+                auto row = [](int u) { return C::frow(u / (NCH / 2), band * FB) + u % (NCH / 2) * RPU; };
+                Acc old[NCH][4];
+                if constexpr (RD) {
 #pragma unroll
-            for (int u = 0; u < NCH; ++u) {
-                const int row = C::frow(u / (NCH / 2), band * FB) + u % (NCH / 2) * RPU;
-                const f32x4 v = staged(reg, u);
-                const Acc w[4] = {v[0], v[1], v[2], v[3]};
-                put4<CT, Acc>(q + (int64_t)row * P.ldc * EB, w, beta, false);
-            }
-        });
+                    for (int u = 0; u < NCH; ++u)
+                        if (!EDGE || row(u) < rows) load4<CT, Acc>(q + row(u) * pitch, old[u]);
+                }
+                write_band(bb, reg);
+                wait_lds();
+                plain_barrier();
+#pragma unroll
+                for (int u = 0; u < NCH; ++u) {
+                    const f32x4 v = staged(reg, u);
+                    Acc w[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) w[e] = RD ? v[e] + beta * old[u][e] : v[e];
+                    if (!EDGE || row(u) < rows) put4<CT, Acc>(q + row(u) * pitch, w, beta, false);
+                }
+                if (EDGE && P.n % 4 != 0 && tn * C::BN + C::BN > P.n && col < P.n && col + 4 > P.n) {
+                    // the last chunk of a row that ends inside it
+#pragma unroll 1
+                    for (int u = 0; u < NCH; ++u) {
+                        const int r = C::frow(u / (NCH / 2), band * FB) + u % (NCH / 2) * RPU;
+                        for (int e = 0; row0 + r < P.m && col + e < P.n; ++e) {
+                            const int rr = br0 + u * RPU;
+                            const Acc v = *(const float *)(reg + rr * RS + ((tid % Q) ^ (rr % 16)) * 16 + e * 4);
+                            char *const qe = q + r * pitch + e * EB;
+                            put_c<CT, Acc>(qe, RD ? v + beta * load_c<CT, Acc>(qe) : v);
+                        }
+                    }
+                }
+            });
+        };
+        using Yes = std::integral_constant<bool, true>;
+        using No = std::integral_constant<bool, false>;
+        if (rd) bands(Yes{}, Yes{});
+        else if (interior) bands(No{}, No{});
+        else bands(Yes{}, No{});
         wait_lds();
         plain_barrier();                              // LDS free for the next unit's loads
         return;
     }
-#pragma unroll 1
-    for (int band = 0; band < NB; ++band) {
+    // one element per lane: a thread's column stays, a wave's elements lie in
+    // one row
+    constexpr int RPE = C::THREADS / C::BN, NE = C::WGM * BR / RPE;
+    static_assert(C::THREADS % C::BN == 0 && C::BN % 64 == 0 && 16 % RPE == 0, "rows per round");
+    const int er = __builtin_amdgcn_readfirstlane(tid / C::BN), e = tid % C::BN;
+    const int row0 = tm * C::BM + er, col = tn * C::BN + e;
+    const int rows = P.m - row0;
+    char *const q = (char *)P.C + row0 * pitch + (int64_t)col * EB;
+    static_for<NB>([&](auto bb) {
+        constexpr int band = decltype(bb)::value;
         char *const reg = lds + (band & 1) * REGION;
-        static_for<NB>([&](auto bb) {
-            if (band == decltype(bb)::value) write_band(bb, reg);
-        });
+        auto row = [](int u) { return C::frow(u / (NE / 2), band * FB) + u % (NE / 2) * RPE; };
+        Acc old[NE];
+        if (rd && col < P.n) {
+#pragma unroll
+            for (int u = 0; u < NE; ++u)
+                if (row(u) < rows) old[u] = load_c<CT, Acc>(q + row(u) * pitch);
+        }
+        write_band(bb, reg);
         wait_lds();
         plain_barrier();
-        // the band's first row in C for each wave row
-        const int r0 = tm * C::BM + C::frow(0, band * FB), r1 = tm * C::BM + C::frow(1, band * FB);
-        if (P.c_vec) {
-            const int col = tn * C::BN + 4 * (tid % Q);
-            char *const q0 = (char *)P.C + ((int64_t)(r0 + br0) * P.ldc + col) * EB;
-            char *const q1 = (char *)P.C + ((int64_t)(r1 + br0) * P.ldc + col) * EB;
-            const int64_t step = (int64_t)RPU * P.ldc * EB;
-            // C's old values (a short batch ahead of their use), edges
-            constexpr int UB = NCH < 4 ? NCH : 4;
-#pragma unroll 1
-            for (int ub = 0; ub < NCH; ub += UB) {
-                Acc old[UB][4];
-                bool full[UB];
-                char *q[UB];
+        if (col < P.n) {
 #pragma unroll
-                for (int u = 0; u < UB; ++u) {
-                    const int x = ub + u, rr = (x < NCH / 2 ? r0 : r1) + br0 + x % (NCH / 2) * RPU;
-                    q[u] = (x < NCH / 2 ? q0 : q1) + x % (NCH / 2) * step;
-                    full[u] = rr < P.m && col + 4 <= P.n;
-                    if (full[u] && rd) load4<CT, Acc>(q[u], old[u]);
-                }
-#pragma unroll
-                for (int u = 0; u < UB; ++u) {
-                    const int x = ub + u, rr = (x < NCH / 2 ? r0 : r1) + br0 + x % (NCH / 2) * RPU;
-                    const f32x4 v = staged(reg, x);
-                    Acc w[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = full[u] && rd ? v[e] + beta * old[u][e] : v[e];
-                    if (full[u]) {
-                        put4<CT, Acc>(q[u], w, beta, false);
-                    } else if (rr < P.m) {
-                        // the last chunk of a row that ends inside it
-                        for (int e = 0; e < 4 && col + e < P.n; ++e) {
-                            Acc y = e == 0 ? w[0] : e == 1 ? w[1] : e == 2 ? w[2] : w[3];
-                            if (rd) y = y + beta * load_c<CT, Acc>(q[u] + e * EB);
-                            put_c<CT, Acc>(q[u] + e * EB, y);
-                        }
-                    }
-                }
-            }
-        } else {
-            // one element per lane and row piece
-            constexpr int NE = C::WGM * BR * C::BN / C::THREADS, UB = 8;
-            static_assert(NE % UB == 0, "whole batches of elements");
-#pragma unroll 1
-            for (int ub = 0; ub < NE; ub += UB) {
-                Acc old[UB];
-                bool in[UB];
-                char *q[UB];
-#pragma unroll
-                for (int u = 0; u < UB; ++u) {
-                    const int c = tid + (ub + u) * C::THREADS, br = c / C::BN, col = tn * C::BN + c % C::BN;
-                    const int row = (br < BR ? r0 : r1) + br % BR;
-                    q[u] = (char *)P.C + ((int64_t)row * P.ldc + col) * EB;
-                    in[u] = row < P.m && col < P.n;
-                    if (in[u] && rd) old[u] = load_c<CT, Acc>(q[u]);
-                }
-#pragma unroll
-                for (int u = 0; u < UB; ++u) {
-                    const int c = tid + (ub + u) * C::THREADS, br = c / C::BN, e = c % C::BN;
-                    Acc w = *(const float *)(reg + br * RS + ((e / 4) ^ (br % 16)) * 16 + e % 4 * 4);
-                    if (rd) w = w + beta * old[u];
-                    if (in[u]) put_c<CT, Acc>(q[u], w);
-                }
+            for (int u = 0; u < NE; ++u) {
+                const int br = er + u * RPE;
+                Acc w = *(const float *)(reg + br * RS + ((e / 4) ^ (br % 16)) * 16 + e % 4 * 4);
+                if (rd) w = w + beta * old[u];
+                if (row(u) < rows) put_c<CT, Acc>(q + row(u) * pitch, w);
             }
         }
-    }
+    });
     wait_lds();
     plain_barrier();                                  // LDS free for the next unit's loads
 }
