@@ -113,9 +113,11 @@ constexpr int MAX_GRID = 1024;           // largest persistent grid
 constexpr int FLAG_REGION = 2 * MAX_GRID * FLAG_STRIDE * 4;
 // Header words.  A flag is raised by storing the call's epoch, derived from
 // HDR_GEN, so flags never need clearing; the last workgroup of a Stream-K
-// launch to finish (counted in HDR_DONE) advances HDR_GEN for the next call,
-// and returns the eight data-parallel tile queue counters HDR_NEXT + c to 0.
-constexpr int HDR_ERR = 0, HDR_GEN = 1, HDR_DONE = 2, HDR_NEXT = 3, XCDS = 8;
+// launch to have read HDR_GEN advances it for the next call, and returns the
+// eight data-parallel tile queue counters HDR_NEXT + c to 0.  Workgroups count
+// themselves in ARRIVALS groups (a word in the unused half of a flag's line
+// each), the groups in HDR_DONE; the counters return to 0 with the last arrival.
+constexpr int HDR_ERR = 0, HDR_GEN = 1, HDR_DONE = 2, HDR_NEXT = 3, XCDS = 8, ARRIVALS = 16;
 // Owners wait on at most this many peers (one 64-lane polling round).
 constexpr int MAX_PEERS = 64;
 
