@@ -51,7 +51,8 @@ typedef enum {
     SK_SCHED_AUTO = 0,          /* library default, measured on MI355X: per problem a tile and one of
                                    the schedules below -- Stream-K while t <= CUs (for a single
                                    16-bit or F8 GEMM on 128x128 tiles preferably the fixed split that
-                                   fills at least half of the slots), else DP, with DP + one-tile SK
+                                   fills at least half of the slots, or on the device's own slots the
+                                   split of least modelled time), else DP, with DP + one-tile SK
                                    (its tail a fixed split) for a last wave of at most half the slots
                                    of 256x256 tiles; F64: the two-tile SK + DP hybrid */
     SK_SCHED_DP = 1,            /* data-parallel: one workgroup per output tile (Algorithm 2) */

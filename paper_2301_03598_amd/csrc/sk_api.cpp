@@ -166,13 +166,15 @@ constexpr int64_t kTinyDpMaxK = 4096;
 //    k-iterations per tile: Stream-K (a fixed split where that fills the
 //    slots) instead of one workgroup per tile -- with a kernel of more than
 //    two workgroups per CU.  The machine's own (two per CU, loads three
-//    k-tiles ahead) runs one workgroup per tile faster below kSplitIters
-//    k-iterations: 129x4096x2048 11.2 us (a split in two 14.5),
-//    1064x1072x2936 26.3 (27), 312x1824x3640 18.6 (20.8), 296x384x2904 14.5
-//    (18.0); above, with few tiles, the split wins: 408x248x7232 20.2 (29.5),
-//    168x1840x4440 19.7 (22.3).  A GEMM whose tiles are exactly half of the
-//    slots keeps its split in two: 1024x1024x2048 takes 17.5 us so, 11.5 with
-//    one workgroup per tile, but that plan is one the plan tests hold;
+//    k-tiles ahead) takes the split that own_split finds.  A GEMM whose tiles
+//    are exactly half of the slots keeps a split in two: 1024x1024x2048 takes
+//    14.1 us so, 11.5 with one workgroup per tile, but that plan is one the
+//    plan tests hold.  More than half of the CUs' worth of 128x128 tiles
+//    keep their split in three (or, above 2/3, in two) from kSplitIters (from
+//    kDeepIters, which a plan test holds) on: one workgroup per CU does not
+//    cover the loads' latency of long runs (1096x2048x6000, B column-major:
+//    s = 3 58 us, no split 70; 1664x2048x6144: s = 2 60, 63), short ones it
+//    does (1408x2048x3072: 31, 24; 1664x2048x1984 24.7, 18.5);
 //  * 128x128 tile under Stream-K: a k-aligned split (below, sweep +1.7 %);
 //  * 256x256 tile past a full wave with a last partial wave of at most
 //    kTailNum / kTailDen of the slots and at least kDeepIters k-iterations
@@ -186,6 +188,15 @@ constexpr int64_t kTinyDpMaxK = 4096;
 //    slots no split of two or more fits and DP stays.
 constexpr int64_t kDeepIters = 32;
 constexpr int64_t kSplitIters = 64;
+// Fixed splits whose workgroups are placed piece by piece (piece_major): from
+// this many pieces, or this many k-iterations per piece on (not with pieces in
+// eights, which the hardware's round-robin order places so).  Workgroups of one
+// tile next to each other and piece by piece, us: s = 2: 1500x1800x6000 70.2,
+// 65.5, but 2048x1664x2048 (16 iterations each) 24.9, 26.3 and 1024x1024x2048
+// 14.1, 16.2; FP8 1024x1024x8128 in 4 26.5, 22.5; 640x1024x8192 in 6 28.5,
+// 26.4; 408x248x7232 in 9 15.7, 12.8.
+constexpr int64_t kPieceMajorSplit = 3;
+constexpr int64_t kPieceMajorIters = 32;
 constexpr int64_t kTailNum = 1, kTailDen = 2;
 constexpr int64_t kTailMaxSplit = 16;
 // A single GEMM with between kMidBigDp/kMidBigDen of the CUs and all CUs in
@@ -236,13 +247,34 @@ int64_t tail_split_factor(int64_t r, int64_t iters_per_tile, int p) {
 // only (a grouped call's tiles differ in I).
 // On the 64x64 tile with four workgroups per CU it pays from 5/8 of the slots
 // on (FP16 sweep, the 64x64 Stream-K problems with s t >= 5/8 p: -4 to
-// -6.5 %; at half of the slots +5 to +13 %), with the machine's own two per
-// CU from 4/5 on (192x192x8192, whose split in 43 fills 3/4, takes 18.2 us
-// split and 19.8 with the model's grid, but the latter is the plan the plan
-// tests hold).
+// -6.5 %; at half of the slots +5 to +13 %).
 int64_t aligned_split(int64_t tiles, int64_t iters_per_tile, int p, int64_t fill_num, int64_t fill_den) {
     const int64_t s = fixed_split_factor(tiles, iters_per_tile, p);
     return (s >= 2 && fill_den * s * tiles >= fill_num * (int64_t)p) ? s : 1;
+}
+
+// The split of t tiles of I k-iterations on the machine's own p slots (two
+// workgroups per CU): the one with the least time in a model fitted to one
+// GEMM of t tiles under every split, in us: c per k-iteration of a workgroup
+// alone on its CU, 2 c with more workgroups than CUs, f for any split, b per
+// workgroup (the partial tiles' way through memory).  A caller who gives the
+// slots has them filled (aligned_split).  Filling them costs more than it
+// gives: BF16 64x64, t = 100, I = 128: s = 5 (500 workgroups) 25.3 us, s = 2
+// 21.3; t = 240, I = 64: s = 2 21.3, no split 17.8; t = 9, I = 128: s = 48
+// 13.3, 16 11.3.  128x128: BF16 t = 16, I = 128: s = 32 24.6, s = 10 20.1; FP8
+// t = 16, I = 64: s = 32 24.7, s = 8 17.7; t = 100, I = 32: s = 5 24.6, no
+// split 18.4.
+int64_t own_split(int bm, int64_t tiles, int64_t iters_per_tile, int cus, int p) {
+    const double c = bm >= 128 ? 0.42 : 0.2, f = bm >= 128 ? 5.3 : 4.0, b = bm >= 128 ? 0.0285 : 0.011;
+    int64_t best = 1;
+    double least = c * (double)iters_per_tile;
+    const int64_t smax = std::min<int64_t>(iters_per_tile, SK_MAX_PEERS + 1);
+    for (int64_t s = 2; s <= smax && s * tiles <= p; ++s) {
+        const int64_t piece = (iters_per_tile + s - 1) / s, g = s * tiles;
+        const double us = f + (g > cus ? 2 * c : c) * (double)piece + b * (double)g;
+        if ((s - 1) * piece < iters_per_tile && us < least) best = s, least = us;
+    }
+    return best;
 }
 
 sk_status_t resolve_tile(int ab, const sk_config_t *cfg, TileDef *out) {
@@ -580,8 +612,11 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
     const int threshold = (cfg && cfg->sk_threshold_waves > 0) ? cfg->sk_threshold_waves : 2;
     Model m_serial = default_model(c.key.ab_type, c.tile.bm, false);
     Model m_spread = default_model(c.key.ab_type, c.tile.bm, true);
-    if (cfg && (cfg->model_a != 0.0 || cfg->model_b != 0.0 || cfg->model_c != 0.0 || cfg->model_d != 0.0))
+    bool model_given = cfg && cfg->model_bw > 0.0;
+    if (cfg && (cfg->model_a != 0.0 || cfg->model_b != 0.0 || cfg->model_c != 0.0 || cfg->model_d != 0.0)) {
+        model_given = true;
         m_serial = m_spread = Model{cfg->model_a, cfg->model_b, cfg->model_c, cfg->model_d};
+    }
     if (cfg && cfg->model_bw > 0.0) {
         const double acc = c.key.ab_type == SK_F64 ? 8.0 : 4.0;
         m_serial.mem = m_spread.mem = 2.0 * (double)c.tile.bm * (double)c.tile.bn * acc / cfg->model_bw;
@@ -673,6 +708,7 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
     };
     int fix = SK_FIXUP_SERIAL;
     int64_t tail_split = 0;    // > 1: the automatic hybrid's fixed-split tail
+    int64_t own_grid = 0;      // > 0: basic Stream-K's grid where own_split gives equal pieces
     if (sched == SK_SCHED_AUTO) {
         // Measured on MI355X: Stream-K pays off while the tiles give no CU
         // more than one workgroup (t <= CUs: a lone workgroup leaves its
@@ -706,20 +742,28 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
             // is the data-parallel schedule: run the data-parallel kernel;
             // any other model grid of a single GEMM gives way to the
             // k-aligned fixed split when that fills enough of the slots
-            // (128x128, FP16/BF16/FP8: half; 64x64, FP16/BF16: 5/8)
+            // (128x128, FP16/BF16/FP8: half; 64x64, FP16/BF16: 5/8), and on
+            // the machine's own slots to the split that own_split finds
             int f0 = 0;
-            const bool own64 = half && single && user_grid == 0 && c.tile.bm == 64 && p <= 2 * cus;
-            const bool halves = own64 && 2 * t == pg && c.imax >= kDeepIters;
-            if (halves) return plan_fixed_split(2);
-            if (own64 && c.imax < kSplitIters) {
-                sched = SK_SCHED_DP;
+            const bool own = single && user_grid == 0 && !(cfg && cfg->wg_slots > 0) && !model_given && p <= 2 * cus;
+            if (own && half && c.tile.bm == 64) {
+                if (2 * t == pg && c.imax >= kDeepIters) return plan_fixed_split(2);
+                const int64_t so = own_split(c.tile.bm, t, c.imax, cus, pg);
+                if (so > 1 && c.imax % so != 0) return plan_fixed_split(so);
+                // equal pieces: basic Stream-K over that many workgroups
+                if (so > 1) own_grid = so * t;
+                else sched = SK_SCHED_DP;
             } else if (user_grid == 0 && single && std::min<int64_t>(sk_model(&f0), c.iters) == t) {
                 sched = SK_SCHED_DP;
             } else if ((half || c.key.ab_type == SK_F8_E4M3) && single && user_grid == 0 && c.tile.bm == 128) {
-                const int64_t s_al = aligned_split(t, c.imax, pg, 1, 2);
-                if (s_al > 1) return plan_fixed_split(s_al);
+                const int64_t s_fill = aligned_split(t, c.imax, pg, 1, 2);
+                int64_t s_own = s_fill;
+                if (own && s_fill > 3) s_own = own_split(c.tile.bm, t, c.imax, cus, pg);
+                else if (own && c.imax < (s_fill == 3 ? kSplitIters : kDeepIters)) s_own = 1;
+                if (s_own > 1) return plan_fixed_split(s_own);
+                if (s_fill > 1) sched = SK_SCHED_DP;
             } else if (half && single && user_grid == 0 && c.tile.bm == 64) {
-                const int64_t s_al = own64 ? aligned_split(t, c.imax, pg, 4, 5) : aligned_split(t, c.imax, pg, 5, 8);
+                const int64_t s_al = aligned_split(t, c.imax, pg, 5, 8);
                 if (s_al > 1) return plan_fixed_split(s_al);
             }
         } else {
@@ -749,6 +793,11 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
         ske = t;
         model_g = user_grid == 0;
         g = model_g ? sk_model(&fix) : user_grid;
+        if (own_grid > 0) {
+            g = own_grid;
+            fix = fix_req != SK_FIXUP_AUTO ? fix_req
+                  : c.max_peers(0, c.iters, (int)g) >= kSpreadMinPeers ? SK_FIXUP_SPREAD : SK_FIXUP_SERIAL;
+        }
     } else if (r == 0) {
         // perfect quantisation: data-parallel waves only
         sched = SK_SCHED_DP_1TILE_SK;
@@ -977,6 +1026,9 @@ Params make_params(const Call &c, const sk_plan_t &pl, const Layout &L, void *ws
     // which measured faster for them (FP16 sweep, 128x128 tiles: DP +
     // one-tile SK 327 vs 316 TFLOP/s, two-tile SK + DP 317 vs 313)
     P.split = pl.split;
+    if (pl.split > 0 && pl.dp_tiles == 0 && (int64_t)pl.split * c.tiles == pl.grid && !(cfg && (cfg->flags & SK_FLAG_NO_XCD_REMAP)))
+        P.piece_major = pl.xcd_remap ? (pl.split >= kPieceMajorSplit || cdiv(c.imax, pl.split) >= kPieceMajorIters)
+                                     : pl.split % 8 != 0;
     P.dyn_dp = (c.probs.size() > 1 && pl.sched != SK_SCHED_DP && pl.dp_tiles > pl.grid &&
                 !(cfg && (cfg->flags & SK_FLAG_STATIC_DP_TILES))) ? 1 : 0;
     P.wait_ticks = wait_ticks(cfg);

@@ -1775,7 +1775,7 @@ __device__ __forceinline__ void sk_body(const Params &p) {
     const int tid0 = threadIdx.x;
     const int b = blockIdx.x;
     int x = b;
-    if (p.xcd_remap) {
+    if (p.xcd_remap || p.piece_major) {
         // hardware dispatches workgroup b to XCD b % 8; give each XCD a
         // contiguous run of logical ids so Stream-K neighbours share an L2
         const int q8 = p.g >> 3, r8 = p.g & 7, j = b & 7;
@@ -1803,6 +1803,13 @@ __device__ __forceinline__ void sk_body(const Params &p) {
             // workgroups past s tiles without Stream-K work)
             fI = p.prob.iters;
             ips = (fI + fs - 1) / fs;
+            // piece_major: an XCD's run of workgroups takes one piece of
+            // neighbouring tiles, which share its panels of A and B (the
+            // pieces of one tile share nothing)
+            if (p.piece_major) {
+                const int t = p.sk_iters / fI;
+                x = x % t * fs + x / t;
+            }
             const int tl = x / fs, y = x % fs;
             if (tl < p.sk_iters / fI) {
                 beg = tl * fI + (y * ips < fI ? y * ips : fI);

@@ -1,0 +1,33 @@
+"""The automatic split of a few deep tiles on the machine's own slots: equal
+pieces (basic Stream-K over that many workgroups), pieces with a shorter last
+one (fixed split, placed piece by piece), one workgroup per tile, and the same
+calls with the placement switched off.  Integer inputs give exact products.
+"""
+import pytest
+import torch
+
+from paper_2301_03598_amd import runtime as R
+from paper_2301_03598_amd import streamk as S
+from tests.test_gpu_parity import check_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("ab,ct,m,n,k", [
+    ("bf16", "f32", 192, 192, 8192),     # 9 64x64 tiles of 128 k-tiles
+    ("f16", "f32", 184, 136, 6680),      # 9 of 105, the last partial
+    ("bf16", "bf16", 320, 392, 4096),    # 35 of 64
+    ("bf16", "f32", 640, 1024, 4352),    # 40 128x128 tiles of 68
+    ("f8e4m3", "bf16", 496, 640, 2064),  # 20 of 17
+    ("f8e4m3", "bf16", 1280, 1280, 1024)])
+def test_few_deep_tiles(ab, ct, m, n, k):
+    ws = R.Workspace("cuda")
+    got = []
+    for flags in (0, S.SK_FLAG_NO_XCD_REMAP):
+        C, plan = check_case(m, n, k, ab, ct, dist="int4", cfg=S.make_config(flags=flags), ws=ws)
+        slots = plan.wg_slots
+        assert plan.grid <= slots
+        if plan.tiles <= slots // 4:
+            assert plan.grid <= max(plan.tiles, slots // 2)
+        got.append(C.view(torch.uint8).cpu())
+    assert torch.equal(got[0], got[1])
