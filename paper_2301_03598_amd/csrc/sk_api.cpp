@@ -277,12 +277,28 @@ int64_t own_split(int bm, int64_t tiles, int64_t iters_per_tile, int cus, int p)
     return best;
 }
 
+// Whether the caller gives constants of the grid-size model.
+bool model_given(const sk_config_t *cfg) {
+    return cfg->model_a != 0.0 || cfg->model_b != 0.0 || cfg->model_c != 0.0 || cfg->model_d != 0.0 || cfg->model_bw > 0.0;
+}
+
+// A single FP64 GEMM of fewer 128x128 tiles than CUs takes the 64x64 tile: with
+// three workgroups per CU the loads' latency and the fixups overlap, and a
+// fixup moves a quarter of the bytes.  128x128 and 64x64 tiles, us:
+// 128x128x512 15.3, 9.9; 384x384x1024 35.7, 23.9; 640x640x3072 65.3, 53.2;
+// 1500x1000x400 50.5, 31.2; 2050x1546x1034 (221 tiles) 132.5, 117.3; but
+// 2048x2048x1024 (256 tiles, one per CU) 129.3, 144.3, and beyond kF64SmallMaxK
+// the larger tile's half operand traffic wins: 2500x600x6000 302, 352
+// (1200x1200x4000 214, 194).  Calls that give a grid, a schedule, slots or a
+// model keep the default tile.
+constexpr int64_t kF64SmallMaxK = 4096;
+
 sk_status_t resolve_tile(int ab, const sk_config_t *cfg, TileDef *out) {
     int n = 0;
     const TileDef *t = tiles_for(ab, &n);
     if (!t) return SK_ERR_UNSUPPORTED;
     if (!cfg || (cfg->blk_m == 0 && cfg->blk_n == 0 && cfg->blk_k == 0)) {
-        *out = t[0];   // refined by pick_tile for FP16/BF16
+        *out = t[0];   // refined in build_call
         return SK_OK;
     }
     for (int i = 0; i < n; ++i)
@@ -559,6 +575,18 @@ sk_status_t build_call(const sk_gemm_desc_t *d, int32_t count, const sk_config_t
                 c->tile = tiny;
         }
     }
+    if (!tile_given && d[0].ab_type == SK_F64 && !grouped && count == 1 && d[0].k > 0 && d[0].k <= kF64SmallMaxK &&
+        (!cfg || (cfg->sched == SK_SCHED_AUTO && cfg->grid == 0 && cfg->wg_slots <= 0 && !model_given(cfg)))) {
+        const Problem p = to_problem(d[0], c->tile.bm, c->tile.bn, c->tile.bk);
+        const int64_t t = p.m > 0 && p.n > 0 ? cdiv(p.m, c->tile.bm) * (int64_t)p.tiles_n : 0;
+        if (t > 0) {
+            int cus = 0;
+            s = query_cus(&cus);
+            if (s != SK_OK) return s;
+            c->cus = cus;
+            if (t < cus) c->tile = kF64Tiles[1];
+        }
+    }
     c->key = KernelKey{d[0].ab_type, c->tile.bm, c->tile.bn, a_kcontig(d[0]), b_kcontig(d[0]), grouped, false};
     c->probs.resize(count);
     c->tile_prefix.assign(count + 1, 0);
@@ -612,11 +640,8 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
     const int threshold = (cfg && cfg->sk_threshold_waves > 0) ? cfg->sk_threshold_waves : 2;
     Model m_serial = default_model(c.key.ab_type, c.tile.bm, false);
     Model m_spread = default_model(c.key.ab_type, c.tile.bm, true);
-    bool model_given = cfg && cfg->model_bw > 0.0;
-    if (cfg && (cfg->model_a != 0.0 || cfg->model_b != 0.0 || cfg->model_c != 0.0 || cfg->model_d != 0.0)) {
-        model_given = true;
+    if (cfg && (cfg->model_a != 0.0 || cfg->model_b != 0.0 || cfg->model_c != 0.0 || cfg->model_d != 0.0))
         m_serial = m_spread = Model{cfg->model_a, cfg->model_b, cfg->model_c, cfg->model_d};
-    }
     if (cfg && cfg->model_bw > 0.0) {
         const double acc = c.key.ab_type == SK_F64 ? 8.0 : 4.0;
         m_serial.mem = m_spread.mem = 2.0 * (double)c.tile.bm * (double)c.tile.bn * acc / cfg->model_bw;
@@ -745,7 +770,7 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
             // (128x128, FP16/BF16/FP8: half; 64x64, FP16/BF16: 5/8), and on
             // the machine's own slots to the split that own_split finds
             int f0 = 0;
-            const bool own = single && user_grid == 0 && !(cfg && cfg->wg_slots > 0) && !model_given && p <= 2 * cus;
+            const bool own = single && user_grid == 0 && !(cfg && (cfg->wg_slots > 0 || model_given(cfg))) && p <= 2 * cus;
             if (own && half && c.tile.bm == 64) {
                 if (2 * t == pg && c.imax >= kDeepIters) return plan_fixed_split(2);
                 const int64_t so = own_split(c.tile.bm, t, c.imax, cus, pg);

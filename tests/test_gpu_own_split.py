@@ -1,7 +1,8 @@
 """The automatic split of a few deep tiles on the machine's own slots: equal
 pieces (basic Stream-K over that many workgroups), pieces with a shorter last
 one (fixed split, placed piece by piece), one workgroup per tile, and the same
-calls with the placement switched off.  Integer inputs give exact products.
+calls with the placement switched off; FP64's tile.  Integer inputs give exact
+products.
 """
 import pytest
 import torch
@@ -31,3 +32,11 @@ def test_few_deep_tiles(ab, ct, m, n, k):
             assert plan.grid <= max(plan.tiles, slots // 2)
         got.append(C.view(torch.uint8).cpu())
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("m,n,k,blk", [
+    (128, 128, 16, 64), (384, 384, 1024, 64), (126, 786, 888, 64), (2050, 1546, 64, 64),
+    (256, 256, 4098, 128), (2048, 2048, 64, 128)])
+def test_f64_tile(m, n, k, blk):
+    _, plan = check_case(m, n, k, "f64", "f64", dist="int4", ws=R.Workspace("cuda"))
+    assert plan.blk_m == blk
