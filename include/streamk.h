@@ -54,7 +54,8 @@ typedef enum {
                                    fills at least half of the slots, or on the device's own slots the
                                    split of least modelled time), else DP, with DP + one-tile SK
                                    (its tail a fixed split) for a last wave of at most half the slots
-                                   of 256x256 tiles; F64: the two-tile SK + DP hybrid */
+                                   of 256x256 tiles; F64: the two-tile SK + DP hybrid, for few
+                                   64x64 tiles on the device's own slots the split as above */
     SK_SCHED_DP = 1,            /* data-parallel: one workgroup per output tile (Algorithm 2) */
     SK_SCHED_SK = 2,            /* basic Stream-K over all tiles (Algorithm 5), g from the model */
     SK_SCHED_DP_1TILE_SK = 3,   /* full DP waves, then SK over the remaining tiles on g = p */

@@ -253,25 +253,32 @@ int64_t aligned_split(int64_t tiles, int64_t iters_per_tile, int p, int64_t fill
     return (s >= 2 && fill_den * s * tiles >= fill_num * (int64_t)p) ? s : 1;
 }
 
-// The split of t tiles of I k-iterations on the machine's own p slots (two
-// workgroups per CU): the one with the least time in a model fitted to one
-// GEMM of t tiles under every split, in us: c per k-iteration of a workgroup
-// alone on its CU, 2 c with more workgroups than CUs, f for any split, b per
-// workgroup (the partial tiles' way through memory).  A caller who gives the
-// slots has them filled (aligned_split).  Filling them costs more than it
-// gives: BF16 64x64, t = 100, I = 128: s = 5 (500 workgroups) 25.3 us, s = 2
-// 21.3; t = 240, I = 64: s = 2 21.3, no split 17.8; t = 9, I = 128: s = 48
-// 13.3, 16 11.3.  128x128: BF16 t = 16, I = 128: s = 32 24.6, s = 10 20.1; FP8
-// t = 16, I = 64: s = 32 24.7, s = 8 17.7; t = 100, I = 32: s = 5 24.6, no
-// split 18.4.
-int64_t own_split(int bm, int64_t tiles, int64_t iters_per_tile, int cus, int p) {
-    const double c = bm >= 128 ? 0.42 : 0.2, f = bm >= 128 ? 5.3 : 4.0, b = bm >= 128 ? 0.0285 : 0.011;
+// The split of t tiles of I k-iterations on the machine's own p slots: the one
+// with the least time in a model fitted to one GEMM of t tiles under every
+// split, in us: c per k-iteration of a workgroup alone on its CU, share[j] c
+// with j more on some CUs, f for any split, b per workgroup (the partial tiles'
+// way through memory).  A caller who gives the slots has them filled
+// (aligned_split).  Filling them costs more than it gives: BF16 64x64, t = 100,
+// I = 128: s = 5 (500 workgroups) 25.3 us, s = 2 21.3; t = 240, I = 64: s = 2
+// 21.3, no split 17.8; t = 9, I = 128: s = 48 13.3, 16 11.3.  128x128: BF16
+// t = 16, I = 128: s = 32 24.6, s = 10 20.1; FP8 t = 16, I = 64: s = 32 24.7,
+// s = 8 17.7; t = 100, I = 32: s = 5 24.6, no split 18.4.  FP64 64x64 (the
+// grid model's even split, then the best): t = 36, I = 64 24.7, s = 6 17.2;
+// t = 64, I = 32 24.5, s = 4 16.0; t = 100, I = 64 29.3, s = 5 26.1; t = 256,
+// I = 32 34.0, no split 22.0.
+struct SplitModel {
+    double c, f, b, share[3];
+};
+constexpr SplitModel kSplitF64 = {0.52, 5.5, 0.0155, {1.0, 1.65, 2.4}};     // 64x64
+constexpr SplitModel kSplit64 = {0.2, 4.0, 0.011, {1.0, 2.0, 2.0}};         // 16-bit and FP8 types
+constexpr SplitModel kSplit128 = {0.42, 5.3, 0.0285, {1.0, 2.0, 2.0}};
+int64_t own_split(const SplitModel &m, int64_t tiles, int64_t iters_per_tile, int cus, int p) {
     int64_t best = 1;
-    double least = c * (double)iters_per_tile;
+    double least = m.c * (double)iters_per_tile;
     const int64_t smax = std::min<int64_t>(iters_per_tile, SK_MAX_PEERS + 1);
     for (int64_t s = 2; s <= smax && s * tiles <= p; ++s) {
         const int64_t piece = (iters_per_tile + s - 1) / s, g = s * tiles;
-        const double us = f + (g > cus ? 2 * c : c) * (double)piece + b * (double)g;
+        const double us = m.f + m.share[std::min<int64_t>(2, (g - 1) / cus)] * m.c * (double)piece + m.b * (double)g;
         if ((s - 1) * piece < iters_per_tile && us < least) best = s, least = us;
     }
     return best;
@@ -757,7 +764,17 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
         const bool single = c.probs.size() == 1;
         int64_t sk_tiles = (c.tile.bm <= 64 && c.key.ab_type != SK_F64) ? kTinySkTiles - 1 : cus;
         if (half && c.tile.bm <= 64 && c.imax >= kDeepIters) sk_tiles = std::max<int64_t>(sk_tiles, 3 * (int64_t)cus / 2 - 1);
-        if (c.key.ab_type == SK_F64) sched = SK_SCHED_2TILE_SK_DP;
+        const bool own = single && user_grid == 0 && !(cfg && (cfg->wg_slots > 0 || model_given(cfg)));
+        if (c.key.ab_type == SK_F64) {
+            sched = SK_SCHED_2TILE_SK_DP;
+            // few 64x64 tiles: the split that own_split finds, as below
+            if (own && c.tile.bm == 64 && t <= cus) {
+                const int64_t so = own_split(kSplitF64, t, c.imax, cus, pg);
+                if (so > 1 && c.imax % so != 0) return plan_fixed_split(so);
+                sched = so > 1 ? SK_SCHED_SK : SK_SCHED_DP;
+                if (so > 1) own_grid = so * t;
+            }
+        }
         else if (half && single && user_grid == 0 && c.tile.bm >= 256 && t <= cus &&
                  kMidBigDen * t >= kMidBigDp * (int64_t)cus)
             sched = SK_SCHED_DP;
@@ -770,10 +787,10 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
             // (128x128, FP16/BF16/FP8: half; 64x64, FP16/BF16: 5/8), and on
             // the machine's own slots to the split that own_split finds
             int f0 = 0;
-            const bool own = single && user_grid == 0 && !(cfg && (cfg->wg_slots > 0 || model_given(cfg))) && p <= 2 * cus;
-            if (own && half && c.tile.bm == 64) {
+            const bool two = own && p <= 2 * cus;      // two workgroups per CU
+            if (two && half && c.tile.bm == 64) {
                 if (2 * t == pg && c.imax >= kDeepIters) return plan_fixed_split(2);
-                const int64_t so = own_split(c.tile.bm, t, c.imax, cus, pg);
+                const int64_t so = own_split(kSplit64, t, c.imax, cus, pg);
                 if (so > 1 && c.imax % so != 0) return plan_fixed_split(so);
                 // equal pieces: basic Stream-K over that many workgroups
                 if (so > 1) own_grid = so * t;
@@ -783,8 +800,8 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
             } else if ((half || c.key.ab_type == SK_F8_E4M3) && single && user_grid == 0 && c.tile.bm == 128) {
                 const int64_t s_fill = aligned_split(t, c.imax, pg, 1, 2);
                 int64_t s_own = s_fill;
-                if (own && s_fill > 3) s_own = own_split(c.tile.bm, t, c.imax, cus, pg);
-                else if (own && c.imax < (s_fill == 3 ? kSplitIters : kDeepIters)) s_own = 1;
+                if (two && s_fill > 3) s_own = own_split(kSplit128, t, c.imax, cus, pg);
+                else if (two && c.imax < (s_fill == 3 ? kSplitIters : kDeepIters)) s_own = 1;
                 if (s_own > 1) return plan_fixed_split(s_own);
                 if (s_fill > 1) sched = SK_SCHED_DP;
             } else if (half && single && user_grid == 0 && c.tile.bm == 64) {
