@@ -107,7 +107,7 @@ typedef struct {
  *                   F64 128x128x16 (default; AUTO takes 64x64x16 for a single
  *                   GEMM of fewer such tiles than CUs), 64x64x16; F16/BF16 256x256x64,
  *                   128x128x64, 64x64x64; F8 256x256x128, 128x128x128,
- *                   64x64x128 (the 64x64 tiles only when asked for).  F16/BF16/F8
+ *                   64x64x128 (F8's 64x64 only when asked for).  F16/BF16/F8
  *                   default: the 128x128 tile unless the problem has at least 2
  *                   (F16/BF16) or 8 (F8) full waves of those tiles (t >= 2 p,
  *                   t >= 8 p), then the 256x256 tile.

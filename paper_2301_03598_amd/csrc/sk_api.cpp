@@ -24,12 +24,12 @@ struct TileDef {
 // automatic choice takes the second (128x128) tile unless the problem fills
 // at least kBigTileWaves full waves of it (in build_call): the 256x256 tile
 // moves half the operand bytes per flop, which wins once quantisation no
-// longer matters (FP8 8192^3: 1994 vs 1631 TFLOP/s row/row, 2300 vs 2086
-// row/col), while the 128x128 tile fills the machine on smaller problems.
-// The 64x64 tiles of the 16-bit and FP8 types are never the automatic
-// choice; they serve callers (and the autotuner) that pick them: a second,
-// smaller-tile kernel for problems too small or too memory-bound to fill
-// the machine with the larger tiles.
+// longer matters (FP8 8192^3, before the two-group MAC loop: 1994 vs 1631
+// TFLOP/s row/row, 2300 vs 2086 row/col), while the 128x128 tile fills the
+// machine on smaller problems.  The 64x64 tiles serve problems too small or too
+// memory-bound to fill the machine with the larger ones: the automatic choice
+// for small FP16/BF16 and FP64 GEMMs; FP8's is for callers (and the autotuner)
+// that pick it.
 const TileDef kF64Tiles[] = {{128, 128, 16}, {64, 64, 16}};
 const TileDef k16Tiles[] = {{256, 256, 64}, {128, 128, 64}, {64, 64, 64}};
 const TileDef kF8Tiles[] = {{256, 256, 128}, {128, 128, 128}, {64, 64, 128}};
@@ -128,8 +128,9 @@ sk_status_t validate(const sk_gemm_desc_t &d) {
     return SK_OK;
 }
 
-// Workgroups of a tile's kernel that fit one CU by LDS alone (two k-tile
-// buffers of (BM + BN) 128-byte rows; 160 KiB per CU).
+// Workgroups of a tile's kernel that fit one CU by LDS, counted with two k-tile
+// buffers of (BM + BN) 128-byte rows (160 KiB per CU): how given wg_slots are
+// turned into a CU count, whatever the kernels' own buffer counts are.
 int lds_wgs_per_cu(const TileDef &t) {
     const int lds = 2 * (t.bm + t.bn) * 128;
     return std::max(1, (160 * 1024) / lds);
@@ -319,9 +320,10 @@ sk_status_t resolve_tile(int ab, const sk_config_t *cfg, TileDef *out) {
 // Resident workgroup slots of a kernel on the current device (cached).
 struct SlotKey {
     int dev, ab, bm;
-    bool akc, bkc, grouped;
+    bool akc, bkc, grouped, shallow;
     bool operator==(const SlotKey &o) const {
-        return dev == o.dev && ab == o.ab && bm == o.bm && akc == o.akc && bkc == o.bkc && grouped == o.grouped;
+        return dev == o.dev && ab == o.ab && bm == o.bm && akc == o.akc && bkc == o.bkc && grouped == o.grouped &&
+               shallow == o.shallow;
     }
 };
 std::mutex g_slot_mu;
@@ -350,7 +352,7 @@ sk_status_t query_cus(int *cus) {
 sk_status_t query_slots(const KernelKey &key, int *slots) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return SK_ERR_HIP;
-    SlotKey sk_{dev, key.ab_type, key.bm, key.a_kc, key.b_kc, key.grouped};
+    SlotKey sk_{dev, key.ab_type, key.bm, key.a_kc, key.b_kc, key.grouped, key.shallow};
     {
         std::lock_guard<std::mutex> lk(g_slot_mu);
         for (auto &e : g_slot_cache)
@@ -375,23 +377,23 @@ sk_status_t query_slots(const KernelKey &key, int *slots) {
 
 int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// The 16-bit and FP8 64x64 data-parallel kernel is built with four k-tile
-// buffers (two workgroups per CU) and with two (more): the deep one while the
-// tiles are at most two per CU, where its longer lead hides the loads'
-// latency (448 tiles of 34 k-tiles 22.3 us against 24.9), the shallow one
-// beyond, where the other resident workgroups do (693 tiles of 20 k-tiles
-// 17.2 us against 19.0).
+// The 16-bit and FP8 64x64 kernels are built with four k-tile buffers (two
+// workgroups per CU) and with two (more): the deep one while the workgroups are
+// at most two per CU, where its longer lead hides the loads' latency (448 tiles
+// of 34 k-tiles 22.3 us against 24.9), the shallow one beyond, where the other
+// resident workgroups do (693 tiles of 20 k-tiles 17.2 us against 19.0) and
+// where a Stream-K grid of that size is only resident with it.
 constexpr int64_t kDeepTilesPerCu = 2;
 
 // (cus: the device's CU count where the caller knows it, else 0)
 sk_status_t kernel_for(KernelKey key, const sk_plan_t &pl, int cus, KernelEntry *e) {
     key.dp_only = pl.sched == SK_SCHED_DP;
-    if (key.dp_only && key.bm == 64 && key.ab_type != SK_F64) {
+    if (key.bm == 64 && key.ab_type != SK_F64) {
         if (cus <= 0) {
             const sk_status_t s = query_cus(&cus);
             if (s != SK_OK) return s;
         }
-        key.shallow = pl.tiles > kDeepTilesPerCu * cus;
+        key.shallow = pl.grid > kDeepTilesPerCu * cus;
     }
     *e = find_kernel(key);
     return e->launch ? SK_OK : SK_ERR_UNSUPPORTED;
@@ -675,6 +677,17 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
             sk_status_t s = query_slots(c.key, &p);
             if (s == SK_OK) s = query_cus(&cus);
             if (s != SK_OK) return s;
+            // a grid or split of the caller's that takes more slots than the
+            // deep 64x64 kernel has: the shallow one's
+            const int64_t sp = cfg ? cfg->split : 0;
+            if (c.tile.bm == 64 && c.key.ab_type != SK_F64 &&
+                (user_grid > p || (sched == SK_SCHED_FIXED_SPLIT && sp * t > p) ||
+                 (sched == SK_SCHED_DP_1TILE_SK && sp > 1 && sp * (t % p) > p))) {
+                KernelKey ks = c.key;
+                ks.shallow = true;
+                s = query_slots(ks, &p);
+                if (s != SK_OK) return s;
+            }
         } else {
             cus = p / lds_wgs_per_cu(c.tile);
         }

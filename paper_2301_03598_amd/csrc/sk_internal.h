@@ -104,10 +104,10 @@ struct Params {
 
 constexpr int FLAG_STRIDE = 16;          // ints between flags (64 bytes)
 constexpr int WS_HEADER = 256;           // header words and padding
-constexpr int THREADS = 256;             // 4 wave64 per workgroup
 constexpr int MAX_GRID = 1024;           // largest persistent grid
 // The flag region [WS_HEADER, WS_HEADER + FLAG_REGION) is reserved in every
-// workspace whatever the schedule, so nothing but flags is ever stored there:
+// workspace whatever the schedule, so nothing but flags (and, during a launch,
+// the arrival counters) is ever stored there:
 // flag x (x < MAX_GRID) belongs to the partial tile workgroup x stores for
 // its first segment, flag MAX_GRID + x to the one it stores for its last
 // segment (distributed fixup only).

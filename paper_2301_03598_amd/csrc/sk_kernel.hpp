@@ -108,10 +108,11 @@ struct Cfg {
     // 256 tiles of 32 k-tiles 19.6 us with two buffers behind a draining
     // barrier, 12.4 with three, 11.5 with four.  With more tiles than
     // that, more resident workgroups hide the latency better: its
-    // data-parallel kernel is also built with two buffers (NS_; 693 tiles of
+    // kernels are also built with two buffers (NS_; 693 tiles of
     // 20 k-tiles 17.2 us against 18.1 with three and 19.0 with four).  FP64
     // 128x128: 4096^3 2141 us with three and the draining barrier, 2064 and
-    // 2005 with three and four without it.
+    // 2005 with three and four without it (1896 since the accumulators stay in
+    // VGPRs).
     static constexpr int NSTAGE = NS_ ? NS_ : BM == 64 ? (D == Dt::F64 ? 3 : 4) : D == Dt::F64 ? 4 : 2;
     static constexpr int LDS = NSTAGE * STAGE;
     // the eight-wave 256x256 tiles: the two-group MAC loop (mac_loop_pp)
@@ -251,7 +252,8 @@ __device__ __forceinline__ void mfma_step(typename C::Frag (&acc)[C::FM][C::FN],
 // replaces lost a fifth of its time to the fragment reads behind that barrier;
 // BF16 881 us, FP8 (four waves) 583.  Here the length of the memory part
 // decides: with the edge tests in every load BF16 took 777 us, without them
-// (WHOLE) 727 (1511 TFLOP/s), FP8 397 (2768).  The 16x16 MFMA forms draw less
+// (WHOLE) 727 (1511 TFLOP/s), FP8 397 (2768); with the epilogue below 714 and
+// 375 (1540 and 2930).  The 16x16 MFMA forms draw less
 // power than the 32x32 ones, and power sets the clock: MFMAs alone from
 // registers on N(0,1) values 2064 against 1767 TFLOP/s.  On zero inputs the
 // same BF16 kernel takes 565 us; its MFMAs and barriers alone, no loads, 500.
@@ -608,7 +610,8 @@ __device__ __forceinline__ void mac_loop_pp(const Problem &P, int tm, int tn, in
 //
 // Measured (against one draining barrier per k-tile): FP8 4096x1024x4096 31.4
 // -> 23.4 us, 3072^3 54.5 -> 44.5, FP16 3240x1640x5808 107 -> 98.8, BF16
-// 256x256x65536 35.8 -> 28.5, 8192^3 on this tile 1098 -> 979.  A barrier in
+// 256x256x65536 35.8 -> 28.5, 8192^3 on this tile 1098 -> 979 (with the
+// epilogue and fixup below the first now takes 19.9, the fourth 26.7).  A barrier in
 // every phase (five half-tiles more in flight): 25.4, 45.6, 104, 28.0, 1000;
 // raised wave priority around the MFMAs: 8192^3 1426.
 // ---------------------------------------------------------------------------

@@ -40,3 +40,15 @@ def test_few_deep_tiles(ab, ct, m, n, k):
 def test_f64_tile(m, n, k, blk):
     _, plan = check_case(m, n, k, "f64", "f64", dist="int4", ws=R.Workspace("cuda"))
     assert plan.blk_m == blk
+
+
+@pytest.mark.parametrize("ab,ct,bk", [("bf16", "f32", 64), ("f8e4m3", "bf16", 128)])
+def test_grids_of_more_than_two_64_workgroups_per_cu(ab, ct, bk):
+    # the caller's grid or split: the kernel that keeps them all resident
+    ws = R.Workspace("cuda")
+    blk = (64, 64, bk)
+    for cfg, g in ((S.make_config(sched="sk", blk=blk, grid=700), 700),
+                   (S.make_config(sched="fs", blk=blk, split=3), 3 * 240)):
+        _, plan = check_case(1024, 944, 5 * bk - 16, ab, ct, dist="int4", cfg=cfg, ws=ws)
+        assert plan.grid == g <= plan.wg_slots
+    ws.check()
