@@ -584,7 +584,9 @@ sk_status_t build_call(const sk_gemm_desc_t *d, int32_t count, const sk_config_t
                 c->tile = tiny;
         }
     }
-    if (!tile_given && d[0].ab_type == SK_F64 && !grouped && count == 1 && d[0].k > 0 && d[0].k <= kF64SmallMaxK &&
+    // (also where a grouped call has one problem: sk_plan and sk_workspace_size
+    // size that call and sk_gemm alike)
+    if (!tile_given && d[0].ab_type == SK_F64 && count == 1 && d[0].k > 0 && d[0].k <= kF64SmallMaxK &&
         (!cfg || (cfg->sched == SK_SCHED_AUTO && cfg->grid == 0 && cfg->wg_slots <= 0 && !model_given(cfg)))) {
         const Problem p = to_problem(d[0], c->tile.bm, c->tile.bn, c->tile.bk);
         const int64_t t = p.m > 0 && p.n > 0 ? cdiv(p.m, c->tile.bm) * (int64_t)p.tiles_n : 0;
