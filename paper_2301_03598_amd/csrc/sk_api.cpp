@@ -385,10 +385,12 @@ int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // where a Stream-K grid of that size is only resident with it.
 constexpr int64_t kDeepTilesPerCu = 2;
 
+bool two_builds(const KernelKey &key) { return key.bm == 64 && key.ab_type != SK_F64; }
+
 // (cus: the device's CU count where the caller knows it, else 0)
 sk_status_t kernel_for(KernelKey key, const sk_plan_t &pl, int cus, KernelEntry *e) {
     key.dp_only = pl.sched == SK_SCHED_DP;
-    if (key.bm == 64 && key.ab_type != SK_F64) {
+    if (two_builds(key)) {
         if (cus <= 0) {
             const sk_status_t s = query_cus(&cus);
             if (s != SK_OK) return s;
@@ -632,7 +634,15 @@ constexpr int64_t kSpreadMinPeers = 2;
 // No plan may give a tile's owner more than SK_MAX_PEERS peers: the model's
 // grid search skips such grids, the automatic schedule avoids them, and an
 // explicit grid or hybrid that needs them is rejected.
-sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
+//
+// The device's own slots of a tile with two builds (kernel_for) are the deep
+// one's, or the shallow one's where those hold all tiles at once and the deep
+// one's do not: there a hybrid or a smaller grid splits tiles that could be
+// whole.  Basic Stream-K, deep and shallow slots, us: BF16 600 tiles of 40
+// k-tiles 40.7, 30.9, 900 of 20 25.2, 22.9, F8 600 of 40 45.9, 31.1 (520 of 20:
+// BF16 17.9, 19.3, F8 19.9, 18.8); 240 of 64, all resident either way, BF16
+// 24.1, 36.7; 1600 of 16 34.9, 35.2.  `shallow`: the shallow one's in any case.
+sk_status_t plan_on(const Call &c, const sk_config_t *cfg, bool shallow, sk_plan_t *pl) {
     std::memset(pl, 0, sizeof(*pl));
     pl->blk_m = c.tile.bm;
     pl->blk_n = c.tile.bn;
@@ -679,16 +689,13 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
             sk_status_t s = query_slots(c.key, &p);
             if (s == SK_OK) s = query_cus(&cus);
             if (s != SK_OK) return s;
-            // a grid or split of the caller's that takes more slots than the
-            // deep 64x64 kernel has: the shallow one's
-            const int64_t sp = cfg ? cfg->split : 0;
-            if (c.tile.bm == 64 && c.key.ab_type != SK_F64 &&
-                (user_grid > p || (sched == SK_SCHED_FIXED_SPLIT && sp * t > p) ||
-                 (sched == SK_SCHED_DP_1TILE_SK && sp > 1 && sp * (t % p) > p))) {
+            if (two_builds(c.key)) {
                 KernelKey ks = c.key;
+                int all = 0;
                 ks.shallow = true;
-                s = query_slots(ks, &p);
+                s = query_slots(ks, &all);
                 if (s != SK_OK) return s;
+                if (shallow || (t > p && t <= all)) p = all;
             }
         } else {
             cus = p / lds_wgs_per_cu(c.tile);
@@ -928,6 +935,15 @@ sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
     pl->fixup = fix;
     pl->max_peers = (int32_t)mp;
     return SK_OK;
+}
+
+// A call that does not fit the deep build's slots (its grid or split, or a
+// hybrid's last tiles over so few workgroups that an owner would have too many
+// peers) is planned on the shallow one's.
+sk_status_t plan_call(const Call &c, const sk_config_t *cfg, sk_plan_t *pl) {
+    const sk_status_t s = plan_on(c, cfg, false, pl);
+    if (s == SK_OK || !two_builds(c.key) || (cfg && cfg->wg_slots > 0)) return s;
+    return plan_on(c, cfg, true, pl);
 }
 
 // Plans of single GEMMs, cached by everything planning reads (device,
