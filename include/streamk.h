@@ -118,7 +118,11 @@ typedef struct {
  *                   Must not exceed wg_slots (a fixup waits for other
  *                   workgroups, so all g must be co-resident) nor SK_MAX_GRID.
  *  wg_slots         p, resident workgroup slots (CUs x workgroups per CU for
- *                   the chosen kernel); 0 = queried from the current device.
+ *                   the chosen tile); 0 = queried from the current device.
+ *                   Launches in flight together each give their share of the
+ *                   slots that a plan reports.  The 16-bit and F8 64x64 tile
+ *                   is built for two and for more workgroups per CU; its
+ *                   slots are those of the second build.
  *  sk_threshold_waves  full waves w at and above which AUTO / 2TILE use the
  *                   two-tile hybrid (below it, DP + one-tile SK); 0 = 2.
  *  flags            SK_FLAG_* bits.
@@ -206,7 +210,7 @@ typedef struct {
     int32_t sched;            /* resolved schedule (never AUTO) */
     int32_t blk_m, blk_n, blk_k;
     int32_t grid;             /* workgroups launched */
-    int32_t wg_slots;         /* p used for the decision */
+    int32_t wg_slots;         /* p: given, or the tile's on the device */
     int32_t dp_first;         /* 1: each WG runs its DP tiles before its SK range */
     int32_t xcd_remap;        /* 1: logical ids grouped per XCD */
     int64_t tiles;            /* output tiles over all problems */

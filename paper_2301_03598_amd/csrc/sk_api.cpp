@@ -387,16 +387,35 @@ constexpr int64_t kDeepTilesPerCu = 2;
 
 bool two_builds(const KernelKey &key) { return key.bm == 64 && key.ab_type != SK_F64; }
 
-// (cus: the device's CU count where the caller knows it, else 0)
+// The slots of both builds on the current device.
+sk_status_t query_builds(KernelKey key, int *deep, int *all) {
+    key.shallow = false;
+    const sk_status_t s = query_slots(key, deep);
+    if (s != SK_OK) return s;
+    key.shallow = true;
+    return query_slots(key, all);
+}
+
+// wg_slots count the shallow build's slots.  A deep workgroup takes the room of
+// two, so a Stream-K launch on a share of the slots, whose workgroups have to be
+// resident together with those of the launches on the other shares, takes the
+// deep build up to half of its share.  (cus: the device's CU count where the
+// caller knows it, else 0)
 sk_status_t kernel_for(KernelKey key, const sk_plan_t &pl, int cus, KernelEntry *e) {
-    key.dp_only = pl.sched == SK_SCHED_DP;
-    if (two_builds(key)) {
+    const bool dp = pl.sched == SK_SCHED_DP;
+    if (two_builds(key) && dp) {
         if (cus <= 0) {
             const sk_status_t s = query_cus(&cus);
             if (s != SK_OK) return s;
         }
         key.shallow = pl.grid > kDeepTilesPerCu * cus;
+    } else if (two_builds(key)) {
+        int deep = 0, all = 0;
+        const sk_status_t s = query_builds(key, &deep, &all);
+        if (s != SK_OK) return s;
+        key.shallow = (int64_t)pl.grid * all > (int64_t)std::min<int>(pl.wg_slots, all) * deep;
     }
+    key.dp_only = dp;
     *e = find_kernel(key);
     return e->launch ? SK_OK : SK_ERR_UNSUPPORTED;
 }
@@ -689,18 +708,18 @@ sk_status_t plan_on(const Call &c, const sk_config_t *cfg, bool shallow, sk_plan
             sk_status_t s = query_slots(c.key, &p);
             if (s == SK_OK) s = query_cus(&cus);
             if (s != SK_OK) return s;
+            pl->wg_slots = p;
             if (two_builds(c.key)) {
-                KernelKey ks = c.key;
                 int all = 0;
-                ks.shallow = true;
-                s = query_slots(ks, &all);
+                s = query_builds(c.key, &p, &all);
                 if (s != SK_OK) return s;
+                pl->wg_slots = all;
                 if (shallow || (t > p && t <= all)) p = all;
             }
         } else {
             cus = p / lds_wgs_per_cu(c.tile);
+            pl->wg_slots = p;
         }
-        pl->wg_slots = p;
         if (user_grid > p) return SK_ERR_INVALID_VALUE;   // all workgroups must be co-resident
     }
     const int pg = std::min(p, SK_MAX_GRID);   // grids the model may choose

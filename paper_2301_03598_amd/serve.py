@@ -134,7 +134,7 @@ class Server:
             cfg.blk_m, cfg.blk_n, cfg.blk_k = pl.blk_m, pl.blk_n, pl.blk_k
         key = (dtype, cfg.blk_m, cfg.blk_n, cfg.blk_k)
         if key not in self.slots:
-            # (a one-workgroup Stream-K plan reports the kernel's slots)
+            # (a one-workgroup Stream-K plan reports the tile's slots)
             st, pl = S.sk_plan(descs, S.make_config(sched="sk", blk=(cfg.blk_m, cfg.blk_n, cfg.blk_k), grid=1))
             S.check(st, "sk_plan")
             self.slots[key] = pl.wg_slots
