@@ -104,8 +104,8 @@ typedef struct {
  * Launch configuration; every field 0 (or NULL) selects the library default.
  *  sched            sk_sched_t.
  *  blk_m/n/k        tile shape; must be one built for the dtype.  Built:
- *                   F64 128x128x16 (default; AUTO takes 64x64x16 for a single
- *                   GEMM of fewer such tiles than CUs), 64x64x16; F16/BF16 256x256x64,
+ *                   F64 128x128x16 (default; AUTO takes 64x64x16 for most single
+ *                   GEMMs of fewer such tiles than CUs), 64x64x16; F16/BF16 256x256x64,
  *                   128x128x64, 64x64x64; F8 256x256x128, 128x128x128,
  *                   64x64x128 (F8's 64x64 only when asked for).  F16/BF16/F8
  *                   default: the 128x128 tile unless the problem has at least 2

@@ -290,16 +290,35 @@ bool model_given(const sk_config_t *cfg) {
     return cfg->model_a != 0.0 || cfg->model_b != 0.0 || cfg->model_c != 0.0 || cfg->model_d != 0.0 || cfg->model_bw > 0.0;
 }
 
-// A single FP64 GEMM of fewer 128x128 tiles than CUs takes the 64x64 tile: with
-// three workgroups per CU the loads' latency and the fixups overlap, and a
-// fixup moves a quarter of the bytes.  128x128 and 64x64 tiles, us:
-// 128x128x512 15.3, 9.9; 384x384x1024 35.7, 23.9; 640x640x3072 65.3, 53.2;
-// 1500x1000x400 50.5, 31.2; 2050x1546x1034 (221 tiles) 132.5, 117.3; but
-// 2048x2048x1024 (256 tiles, one per CU) 129.3, 144.3, and beyond kF64SmallMaxK
-// the larger tile's half operand traffic wins: 2500x600x6000 302, 352
-// (1200x1200x4000 214, 194).  Calls that give a grid, a schedule, slots or a
-// model keep the default tile.
-constexpr int64_t kF64SmallMaxK = 4096;
+// Whether a single FP64 GEMM of t 128x128 tiles, fewer than CUs, takes the 64x64
+// tile (t64 of them): with three workgroups per CU the loads' latency and the
+// fixups overlap, and a fixup moves a quarter of the bytes.  128x128 and 64x64
+// tiles, us: 128x128x512 15.3, 9.9; 384x384x1024 35.7, 23.9; 640x640x3072 65.3,
+// 53.2; 1500x1000x400 50.5, 31.2.  Where it loses, it is to the larger tile's
+// half operand traffic, with many tiles and long k:
+//  * up to 7/4 CUs' worth of 64x64 tiles it wins to k = 4096 (1024x1536x4096,
+//    384 tiles, 207, 195);
+//  * to k = 1792 up to 13/4 (1664x1664x1536 140, 139; 2050x1546x1034, 825 tiles,
+//    133, 121), from 24 k-tiles on up to 55/16 (1493x2278x400, 864, 66.4, 63.5),
+//    not beyond (2048x1792x1024, 896, 125, 130; 1920x2176x1024, 1020, 130, 145),
+//    nor with few k-tiles (1820x1885x84, 870, 25.2, 29.4), where a last wave of
+//    few tiles is split over all slots;
+//  * longer k only where the 128x128 tiles' padding costs more: an eighth of
+//    their area while all 64x64 tiles are resident (395x4182x2974, 462, 203, 187;
+//    but 1664x1664x2048, none, 182, 198, x4096 338, 401), a thirty-second beyond
+//    (4638x698x1896, 803, 219, 203; 1620x2004x2310, none, 245, 250).
+bool f64_small_tile(int64_t t, int64_t t64, int64_t k, int64_t iters, int64_t cus) {
+    if (t >= cus || k > 4096) return false;
+    if (4 * t64 <= 7 * cus) return true;
+    if (k <= 1792) return 4 * t64 <= 13 * cus || (iters >= 24 && 16 * t64 <= 55 * cus);
+    return t64 <= 3 * cus ? 8 * 4 * t >= 9 * t64 : 32 * 4 * t >= 33 * t64;
+}
+// With fewer k-tiles than this, more 64x64 FP64 tiles than slots, in the range
+// above, run one workgroup per tile rather than the hybrid, whose last few
+// tiles are split over all slots: 2050x1546x64 25.8, 18.0 us, x128 31.8, 24.7,
+// 1664x1920x192 36.6, 32.2; but 4869x578x248 (16 k-tiles, two tiles past the
+// slots) 34.7, 39.3.
+constexpr int64_t kF64DpIters = 16;
 
 sk_status_t resolve_tile(int ab, const sk_config_t *cfg, TileDef *out) {
     int n = 0;
@@ -605,18 +624,19 @@ sk_status_t build_call(const sk_gemm_desc_t *d, int32_t count, const sk_config_t
                 c->tile = tiny;
         }
     }
-    // (also where a grouped call has one problem: sk_plan and sk_workspace_size
-    // size that call and sk_gemm alike)
-    if (!tile_given && d[0].ab_type == SK_F64 && count == 1 && d[0].k > 0 && d[0].k <= kF64SmallMaxK &&
+    // (calls that give a grid, a schedule, slots or a model keep the default
+    // tile; also where a grouped call has one problem: sk_plan and
+    // sk_workspace_size size that call and sk_gemm alike)
+    if (!tile_given && d[0].ab_type == SK_F64 && count == 1 && d[0].k > 0 &&
         (!cfg || (cfg->sched == SK_SCHED_AUTO && cfg->grid == 0 && cfg->wg_slots <= 0 && !model_given(cfg)))) {
-        const Problem p = to_problem(d[0], c->tile.bm, c->tile.bn, c->tile.bk);
-        const int64_t t = p.m > 0 && p.n > 0 ? cdiv(p.m, c->tile.bm) * (int64_t)p.tiles_n : 0;
-        if (t > 0) {
-            int cus = 0;
-            s = query_cus(&cus);
+        const TileDef big = c->tile, tiny = kF64Tiles[1];
+        const Problem p = to_problem(d[0], tiny.bm, tiny.bn, tiny.bk);
+        if (p.m > 0 && p.n > 0) {
+            s = query_cus(&c->cus);
             if (s != SK_OK) return s;
-            c->cus = cus;
-            if (t < cus) c->tile = kF64Tiles[1];
+            if (f64_small_tile(cdiv(p.m, big.bm) * cdiv(p.n, big.bn), cdiv(p.m, tiny.bm) * (int64_t)p.tiles_n, p.k,
+                               p.iters, c->cus))
+                c->tile = tiny;
         }
     }
     c->key = KernelKey{d[0].ab_type, c->tile.bm, c->tile.bn, a_kcontig(d[0]), b_kcontig(d[0]), grouped, false};
@@ -814,6 +834,8 @@ sk_status_t plan_on(const Call &c, const sk_config_t *cfg, bool shallow, sk_plan
                 if (so > 1 && c.imax % so != 0) return plan_fixed_split(so);
                 sched = so > 1 ? SK_SCHED_SK : SK_SCHED_DP;
                 if (so > 1) own_grid = so * t;
+            } else if (own && c.tile.bm == 64 && t > p && 4 * t <= 13 * (int64_t)cus && c.imax < kF64DpIters) {
+                sched = SK_SCHED_DP;
             }
         }
         else if (half && single && user_grid == 0 && c.tile.bm >= 256 && t <= cus &&
