@@ -25,8 +25,6 @@ CXXFLAGS = [
     f"-I{INCLUDE}", f"-I{CSRC}",
     # no packed-FP32 VALU forms anywhere in the device code
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # the LDS-DMA issue names m0 as clobbered, which the compiler remarks on
-    "-Wno-inline-asm",
     # MFMAs accumulate in VGPRs: with the accumulators in AGPRs the compiler
     # copies the whole set there and back around every trip of an FP64 MAC
     # loop (4096^3 2011 us against 1888) and some of it in the 64x64 tiles'

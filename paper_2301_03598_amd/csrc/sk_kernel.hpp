@@ -349,11 +349,19 @@ struct OpDma {
     }
     // One 1 KiB load.  Issued as text: the compiler would otherwise wait,
     // before the reads of one buffer, for loads into others (it keeps too few
-    // of them apart).
+    // of them apart).  Its hazard handling does not see into the text: a vector
+    // instruction that writes rs or so (the readlane of a spilled register) has
+    // to lie five wait states ahead of the load, of which the text holds two.
+    // The nearest lies ten ahead, and a test of the built library's machine
+    // code holds that; the three more in the text (s_nop 3) cost BF16 8192^3 714 ->
+    // 721 us, FP64 4096x4096x2048 962 -> 969, FP16 200x136x520 5.0 -> 5.2.
     __device__ __forceinline__ static void dma(const i32x4 &rs, uint32_t dst, uint32_t vo, uint32_t so) {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // m0 as clobbered: "reserved register"
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                      :: "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(vo), "s"(rs), "s"(__builtin_amdgcn_readfirstlane(so))
                      : "memory", "m0");
+#pragma clang diagnostic pop
     }
     __device__ __forceinline__ uint32_t dst(char *lds, int i) const {
         return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)lds + i * C::DMA_ROUND + w1024;
