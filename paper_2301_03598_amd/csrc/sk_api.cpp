@@ -855,7 +855,8 @@ sk_status_t plan_on(const Call &c, const sk_config_t *cfg, bool shallow, sk_plan
                 if (2 * t == pg && c.imax >= kDeepIters) return plan_fixed_split(2);
                 const int64_t so = own_split(kSplit64, t, c.imax, cus, pg);
                 if (so > 1 && c.imax % so != 0) return plan_fixed_split(so);
-                // equal pieces: basic Stream-K over that many workgroups
+                // equal pieces are the ranges of basic Stream-K over that many
+                // workgroups, and are planned (and placed) as that
                 if (so > 1) own_grid = so * t;
                 else sched = SK_SCHED_DP;
             } else if (user_grid == 0 && single && std::min<int64_t>(sk_model(&f0), c.iters) == t) {

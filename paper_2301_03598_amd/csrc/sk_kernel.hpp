@@ -920,7 +920,6 @@ __device__ __forceinline__ void load4(const char *p, Acc (&v)[4]) {
 // Four consecutive outputs of one row, alpha*acc (+ beta*C), rounded once.
 template <int CT, class Acc>
 __device__ __forceinline__ void put4(char *p, const Acc (&v)[4], Acc beta, bool rd) {
-    constexpr int EB = CBytes<CT>::v;
     Acc w[4];
     if (rd) {
         Acc o[4];
@@ -938,7 +937,6 @@ __device__ __forceinline__ void put4(char *p, const Acc (&v)[4], Acc beta, bool 
         typedef H h4 __attribute__((ext_vector_type(4)));
         *(h4 *)p = h4{(H)(float)w[0], (H)(float)w[1], (H)(float)w[2], (H)(float)w[3]};
     }
-    (void)EB;
 }
 
 // Partial tiles: thread-fragment order, 16-byte chunk v of thread t at
@@ -1009,7 +1007,7 @@ __device__ __forceinline__ typename C::Frag add_peers(typename C::Frag v, const 
 // LDS buffers by LDS-DMA loads, in FIX_PH phases, so its fragments are read
 // with LDS latency instead of one global round trip each.  Each wave stages
 // exactly the chunks its own lanes read back (partial chunk v of thread t
-// sits at v*4096 + 16t in both places), so a wave only waits for its own
+// sits at 16 (THREADS v + t) in both places), so a wave only waits for its own
 // loads; a barrier after the epilogue keeps the next unit's DMA away.
 template <class C>
 struct FixStage {
@@ -1249,7 +1247,6 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
                                              const char *slots, int p0, int p1, char *lds) {
     using Acc = typename C::Acc;
     constexpr int EB = CBytes<CT>::v;
-    constexpr int G = C::FRAG_N / 4;                 // column groups per fragment
     const int lane = tid & 63, wave = tid >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
     const Acc alpha = (Acc)P.alpha, beta = (Acc)P.beta;
     const bool rd = P.beta != 0.0;
@@ -1281,8 +1278,7 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
     }
     // whole rows through the LDS, edge tiles included (the flags are uniform
     // over the workgroup); not on the 64x64 tile, where it measures even with
-    // aligned rows and
-    // 5 % slower without
+    // aligned rows and 5 % slower without
     if (C::BM >= 128 && p0 > p1) {
         store_tile_rows<C, CT>(P, tm, tn, acc, tid, lds, interior);
         return;
@@ -1295,30 +1291,25 @@ __device__ __forceinline__ void store_tile_t(const Problem &P, int tm, int tn,
         if constexpr (j == 0) fix_phase<C>(staged, slots, p0, lds, i, tid);
         const int row = rowl + C::frow(0, i);
         char *rp = (char *)P.C + ((int64_t)row * P.ldc + coll) * EB;
-        {
-            const typename C::Frag f = fix_frag<C>(acc[i][j], slots, p0, p1, lds, i, j, tid);
+        const typename C::Frag f = fix_frag<C>(acc[i][j], slots, p0, p1, lds, i, j, tid);
+        constexpr int co = C::fcol(0, j);                 // column offset from coll
+        Acc v[4];
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const int co = C::fcol(0, j) + 8 * g;     // column offset from coll
-                Acc v[4];
+        for (int e = 0; e < 4; ++e) v[e] = alpha * f[e];
+        if (fast) {
+            put4<CT, Acc>(rp + co * EB, v, beta, rd);
+        } else if (row < P.m) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = alpha * f[4 * g + e];
-                if (fast) {
-                    put4<CT, Acc>(rp + co * EB, v, beta, rd);
-                } else if (row < P.m) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (coll + co + e < P.n) {
-                            char *q = rp + (co + e) * EB;
-                            Acc w = v[e];
-                            if (rd) w = w + beta * load_c<CT, Acc>(q);
-                            put_c<CT, Acc>(q, w);
-                        }
-                    }
+            for (int e = 0; e < 4; ++e) {
+                if (coll + co + e < P.n) {
+                    char *q = rp + (co + e) * EB;
+                    Acc w = v[e];
+                    if (rd) w = w + beta * load_c<CT, Acc>(q);
+                    put_c<CT, Acc>(q, w);
                 }
             }
-            __builtin_amdgcn_sched_barrier(0);
         }
+        __builtin_amdgcn_sched_barrier(0);
     });
 }
 
@@ -1477,7 +1468,7 @@ struct Spread {
             // four consecutive columns of one row
             const f32x4 v = __builtin_bit_cast(f32x4, raw);
             const int row = tm * C::BM + C::frow(wm, fi) + (lane % C::MT);
-            const int col = tn * C::BN + C::fcol(wn, fj) + 8 * sc + 4 * (lane / C::MT);
+            const int col = tn * C::BN + C::fcol(wn, fj) + 4 * (lane / C::MT);
             char *rp = (char *)P.C + ((int64_t)row * P.ldc + col) * EB;
             Acc a[4];
 #pragma unroll
@@ -1518,7 +1509,7 @@ struct Spread {
         } else {
             // four consecutive columns of one row
             row = tm * C::BM + C::frow(wm, fi) + (lane % C::MT);
-            col = tn * C::BN + C::fcol(wn, fj) + 8 * sc + 4 * (lane / C::MT) + e;
+            col = tn * C::BN + C::fcol(wn, fj) + 4 * (lane / C::MT) + e;
         }
         if (row < P.m && col < P.n) {
             char *q = (char *)P.C + ((int64_t)row * P.ldc + col) * EB;
