@@ -739,19 +739,27 @@ __device__ __forceinline__ void mac_loop_half(const Problem &P, int tm, int tn, 
 // The MAC loop of the other tiles over iterations [it0, it1) of one tile
 // (Algorithm 3)
 //
-// NSTAGE k-tile buffers; the loads run LA = NSTAGE - 1 k-tiles ahead, into
-// the buffer of the k-tile before the running one.  A k-tile's k-steps run
+// NSTAGE k-tile buffers; the loads run LA k-tiles ahead, into the buffer of
+// the k-tile before the running one (NSTAGE - 1).  A k-tile's k-steps run
 // with their operand fragments double-buffered in registers (the reads of
 // step s + 1 overlap the MFMAs of step s); before the last step's MFMAs the
 // wave waits for its reads of this k-tile and its loads of the next one, then
 // one barrier, so those MFMAs cover the first fragment reads of the next
 // k-tile.  The barrier itself waits for nothing: a __syncthreads would wait
 // for every load in flight (they write LDS) and undo the lead.
+//
+// With two buffers that would leave a load half a k-tile to land.  EARLY: the
+// loads follow the barrier, behind which the running k-tile's own buffer is
+// free, and have a whole one (64x64 tiles, loads in the first step and behind the
+// barrier, us: BF16 1023x2552x4008, 640 of 63 k-tiles, 58.3, 52.1; FP16
+// 1749x1328x2760, 588 of 44, 39.5, 35.1; 4000x704x1256, 693 of 20, 18.4, 17.9).
 // ---------------------------------------------------------------------------
 template <class C>
 struct RingState {
     OpDma<C, C::AKC, C::BM, 1> da;
     OpDma<C, C::BKC, C::BN, 1> db;
+    static constexpr bool EARLY = C::NSTAGE == 2 && Frag<C>::NSUB > 1;
+    static constexpr int LA = EARLY ? C::NSTAGE : C::NSTAGE - 1;
     static constexpr int DPK = OpDma<C, C::AKC, C::BM, 1>::NL + OpDma<C, C::BKC, C::BN, 1>::NL;   // loads per wave per k-tile
 };
 
@@ -772,7 +780,8 @@ __device__ __forceinline__ void ktile_ring(const RingState<C> &st, Frag<C> (&f)[
                                            typename C::Frag (&acc)[C::FM][C::FN], const char *cur, const char *nx,
                                            char *ld, int t, int t1, int wm, int wn, int lane, uint64_t &abase,
                                            uint64_t &bbase) {
-    constexpr int NSUB = Frag<C>::NSUB, LA = C::NSTAGE - 1;
+    constexpr int NSUB = Frag<C>::NSUB, LA = RingState<C>::LA;
+    constexpr bool EARLY = RingState<C>::EARLY;
     const bool live = WHOLE || t + LA < t1;
     auto loads = [&](int op) {
         if (op == 0) {
@@ -784,9 +793,9 @@ __device__ __forceinline__ void ktile_ring(const RingState<C> &st, Frag<C> (&f)[
         }
     };
     auto landed = [&]() {
-        // k-tile t + 1 has landed; up to LA - 1 newer ones may be in flight
-        if constexpr (WHOLE) wait_loads_lds<(LA - 1) * RingState<C>::DPK>();
-        else wait_newer<LA - 1, RingState<C>::DPK>(t1 - 2 - t);
+        // k-tile t + 1 has landed; up to NSTAGE - 2 newer ones may be in flight
+        if constexpr (WHOLE) wait_loads_lds<(C::NSTAGE - 2) * RingState<C>::DPK>();
+        else wait_newer<C::NSTAGE - 2, RingState<C>::DPK>(t1 - 2 - t);
         plain_barrier();
     };
     if constexpr (NSUB == 1) {
@@ -801,7 +810,7 @@ __device__ __forceinline__ void ktile_ring(const RingState<C> &st, Frag<C> (&f)[
             constexpr int ks = decltype(kk)::value;
             if constexpr (ks + 1 == NSUB) landed();
             read_frags<C>(f[(ks + 1) & 1], ks + 1 < NSUB ? cur : nx, wm, wn, (ks + 1) % NSUB, lane);
-            if constexpr (ks == 0) {
+            if constexpr (ks == (EARLY ? NSUB - 1 : 0)) {
                 loads(0);
                 loads(1);
             }
@@ -813,7 +822,7 @@ __device__ __forceinline__ void ktile_ring(const RingState<C> &st, Frag<C> (&f)[
 template <class C>
 __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int it0, int it1,
                                          typename C::Frag (&acc)[C::FM][C::FN], char *lds, int tid) {
-    constexpr int LA = C::NSTAGE - 1, RING = C::NSTAGE * C::STAGE;
+    constexpr int LA = RingState<C>::LA, RING = C::NSTAGE * C::STAGE;
     const int lane = tid & 63, wave = tid >> 6, wm = wave / C::WGN, wn = wave % C::WGN;
     RingState<C> st;
     st.da.init(P.A, P.lda, tm * C::BM, P.m, P.k, tid);
@@ -835,10 +844,10 @@ __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int i
     Frag<C> f[2];
     read_frags<C>(f[0], lds, wm, wn, 0, lane);
     int t = it0;
-    int cur = 0, nx = C::STAGE % RING, ld = LA * C::STAGE;      // byte offsets of the buffers in turn
+    int cur = 0, nx = C::STAGE % RING, ld = LA * C::STAGE % RING;   // byte offsets of the buffers in turn
     uint64_t ab = (uint64_t)st.da.ub + (it0 + LA) * st.da.ustep, bb = (uint64_t)st.db.ub + (it0 + LA) * st.db.ustep;
     auto turn = [&]() {
-        ld = cur;
+        ld = RingState<C>::EARLY ? nx : cur;
         cur = nx;
         nx = nx + C::STAGE == RING ? 0 : nx + C::STAGE;
     };
@@ -1726,9 +1735,9 @@ struct DpQueue {
 // atomic additions from all XCDs to one word take about 20 ns each, one after
 // the other, and the last of them used to end the launch.  The last of a group
 // counts the group, the last group advances the word.  One count at each
-// workgroup's end and now, us: BF16 197x106x6680 (424 workgroups) 17.7, 14.8;
-// 1024x1024x2048 (512) 16.3, 13.8; 256x256x65536 (256) 28.0, 26.6; FP64
-// 384x384x1024 (192) 36.7, 35.4.
+// workgroup's end and this, us: BF16 197x106x6680 (424 workgroups) 17.9, 13.9;
+// 1024x1024x2048 (512) 16.5, 14.1; 256x256x65536 (256) 27.9, 26.7; FP64
+// 384x384x1024 (192) 36.4, 35.8.
 // ---------------------------------------------------------------------------
 struct Arrival {
     __device__ __forceinline__ static int32_t *word(const Params &p, int b) {
