@@ -847,7 +847,8 @@ __device__ __forceinline__ void mac_loop(const Problem &P, int tm, int tn, int i
     int cur = 0, nx = C::STAGE % RING, ld = LA * C::STAGE % RING;   // byte offsets of the buffers in turn
     uint64_t ab = (uint64_t)st.da.ub + (it0 + LA) * st.da.ustep, bb = (uint64_t)st.db.ub + (it0 + LA) * st.db.ustep;
     auto turn = [&]() {
-        ld = RingState<C>::EARLY ? nx : cur;
+        if constexpr (RingState<C>::EARLY) ld = nx;
+        else ld = cur;
         cur = nx;
         nx = nx + C::STAGE == RING ? 0 : nx + C::STAGE;
     };
