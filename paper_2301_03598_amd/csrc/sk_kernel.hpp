@@ -248,7 +248,7 @@ __device__ __forceinline__ void mfma_step(typename C::Frag (&acc)[C::FM][C::FN],
 // B0 after them) in interval 2c - 2 at the latest.
 //
 // What bounds it, and what it measured (8192^3, B row-major, N(0,1) inputs,
-// one box): the two-buffer loop with one barrier per k-tile that this
+// one machine): the two-buffer loop with one barrier per k-tile that this
 // replaces lost a fifth of its time to the fragment reads behind that barrier;
 // BF16 881 us, FP8 (four waves) 583.  Here the length of the memory part
 // decides: with the edge tests in every load BF16 took 777 us, without them
